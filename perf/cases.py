@@ -11,9 +11,10 @@ Ranges (``draw`` spreads over them, ``listed`` holds fixed points of them):
   of input per call (the sizes of the sweep and of the large-N study).
 * Scan: n = 2^4 ... 2^14, int32 / float32 / float64, inclusive and exclusive,
   up to 2^24 elements per call (2^25 for four-byte types).
-* Tridiagonal: n = 2^4 ... 2^14, float32 and float64, the configuration the
+* Tridiagonal: n = 2^4 ... 2^14 in float32 and 2^4 ... 2^13 in float64 (the
+  library has no float64 solver for longer systems), the configuration the
   library resolves by itself or, for the sizes of the sweep (n = 32 ... 1024),
-  the tuned PCR solver; up to 2^23 unknowns per call.
+  the tuned PCR solver; up to 2^23 float32 or 2^22 float64 unknowns per call.
 * Mixed launches: 4 ... 48 jobs of the serving mix (an operation at random,
   log2 n uniform in 4 ... 14, uneven batches), one launch.
 
@@ -92,8 +93,8 @@ def draw(rng):
                 "exclusive": rng.choice([False, True])}
     if kind == "tri":
         family = rng.choice(["auto", "auto", "auto", "pcr"])
-        n = 1 << (rng.randint(5, 10) if family == "pcr" else rng.randint(4, 14))
         dtype = rng.choice(["f32", "f64"])
+        n = 1 << (rng.randint(5, 10) if family == "pcr" else rng.randint(4, 14 if dtype == "f32" else 13))
         most = TRI_MAX_BYTES // (8 if dtype == "f64" else 4)
         return {"kind": "tri", "n": n, "batch": _batch(rng, n, 1 << 10, most), "dtype": dtype, "family": family}
     return {"kind": "mixed", "jobs": rng.randint(4, 48), "pick": rng.randrange(1 << 20)}
