@@ -126,14 +126,21 @@ __device__ __forceinline__ void store_nt_any(V *p, const V &v) {
 }
 
 // K contiguous 4- or 8-byte values at byte offset voff (16-byte words where
-// the size allows; the constant part of each offset in the scalar operand).
+// the size allows).  The constant part of each offset is added to the vector
+// offset, where it folds into the instruction's immediate: a 16-byte store
+// must not take it from a scalar register.  With a scalar-register offset the
+// compiler lets the very next instruction overwrite the store's data
+// registers, and gfx950 then stored the overwritten value in lanes 12..15 of
+// each 16 (seen in the persistent scan of float64 rows: the first 8 bytes of
+// a word replaced by the v_mov that followed its store); with an immediate it
+// keeps them apart.
 template <typename T, int K>
 __device__ __forceinline__ void buf_load(T (&v)[K], __amdgpu_buffer_rsrc_t r, int voff) {
     constexpr int B = K * (int)sizeof(T);
     if constexpr (B % 16 == 0) {
 #pragma unroll
         for (int w = 0; w < B / 16; ++w) {
-            const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(r, voff, 16 * w, 0);
+            const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(r, voff + 16 * w, 0, 0);
             __builtin_memcpy(&v[w * 16 / (int)sizeof(T)], &x, 16);
         }
     } else if constexpr (B == 8) {
@@ -154,7 +161,7 @@ __device__ __forceinline__ void buf_store(const T (&v)[K], __amdgpu_buffer_rsrc_
         for (int w = 0; w < B / 16; ++w) {
             u32x4 x;
             __builtin_memcpy(&x, &v[w * 16 / (int)sizeof(T)], 16);
-            __builtin_amdgcn_raw_buffer_store_b128(x, r, voff, 16 * w, POLICY);
+            __builtin_amdgcn_raw_buffer_store_b128(x, r, voff + 16 * w, 0, POLICY);
         }
     } else if constexpr (B == 8) {
         u32x2 x;
