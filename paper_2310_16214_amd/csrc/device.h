@@ -103,11 +103,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t group_rsrc(const void *base, l
 // dirty data left in the caches to drain), and 1.5% off the step; the first
 // call of the step (n = 16) is 12% slower with them.  Repeated calls of one
 // kernel on the same buffers show larger gains (n = 16384: 112 -> 95 us), part
-// of which is the input staying cached between the calls.  The scan and
-// tridiagonal kernels keep the default policy: with the hint they measured
-// neutral to 33% slower per call (worst where each lane stores a contiguous
-// chunk, so that one store instruction covers only part of each line) and the
-// step no faster.  Loads keep the default policy: on a plain copy, hinting
+// of which is the input staying cached between the calls.  The hint needs
+// stores that cover whole lines (a lane storing a contiguous chunk of 64
+// bytes, one quarter per instruction, is slower with it): the scan and
+// tridiagonal kernels use it where theirs do.  Loads keep the default policy: on a plain copy, hinting
 // both directions was slower than hinting the stores alone.
 constexpr int kStoreNT = 2;
 
@@ -214,25 +213,45 @@ __device__ __forceinline__ T dpp_row_shr(T v) {
     return per_word(v, [](int x) { return __builtin_amdgcn_update_dpp(0, x, kDppRowShr + D, 0xf, 0xf, false); });
 }
 
-// Inclusive scan over aligned segments of SEG lanes (SEG power of two <= 64),
-// Kogge-Stone shape: shifts 1, 2, 4, 8 inside rows, then the row broadcasts.
-// Must be called with all 64 lanes active.
-template <typename T>
-__device__ __forceinline__ T lanes_scan_ks(T x, int seg, int lane) {
-    const int ls = lane & (seg - 1);
-    if (seg > 1) { T y = dpp_row_shr<1>(x); if (ls >= 1) x += y; }
-    if (seg > 2) { T y = dpp_row_shr<2>(x); if (ls >= 2) x += y; }
-    if (seg > 4) { T y = dpp_row_shr<4>(x); if (ls >= 4) x += y; }
-    if (seg > 8) { T y = dpp_row_shr<8>(x); if (ls >= 8) x += y; }
-    if (seg > 16) {
-        // rows 1 and 3 receive the last lane of rows 0 and 2
-        x += per_word(x, [](int w) { return __builtin_amdgcn_update_dpp(0, w, kDppRowBcast15, 0xa, 0xf, false); });
+// Inclusive scans over aligned segments of seg lanes (a power of two <= 64)
+// of R values per lane, each value's scan on its own, Kogge-Stone shape:
+// shifts 1, 2, 4, 8 inside rows, then the row broadcasts.  With whole rows in
+// a segment (seg >= 16) a lane whose source lies before the row gets 0 from
+// the shift and needs no select.  The R scans are independent, so they go
+// through the network side by side (one dependent DPP step of one value has
+// to wait out the previous one).  Must be called with all 64 lanes active.
+template <typename T, int R>
+__device__ __forceinline__ void lanes_scan_ks(T (&x)[R], int seg, int lane) {
+    if (seg >= 16) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) x[j] += dpp_row_shr<1>(x[j]);
+#pragma unroll
+        for (int j = 0; j < R; ++j) x[j] += dpp_row_shr<2>(x[j]);
+#pragma unroll
+        for (int j = 0; j < R; ++j) x[j] += dpp_row_shr<4>(x[j]);
+#pragma unroll
+        for (int j = 0; j < R; ++j) x[j] += dpp_row_shr<8>(x[j]);
+        if (seg > 16) {
+            // rows 1 and 3 receive the last lane of rows 0 and 2
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+                x[j] += per_word(x[j], [](int w) { return __builtin_amdgcn_update_dpp(0, w, kDppRowBcast15, 0xa, 0xf, false); });
+        }
+        if (seg > 32) {
+            // rows 2 and 3 receive lane 31
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+                x[j] += per_word(x[j], [](int w) { return __builtin_amdgcn_update_dpp(0, w, kDppRowBcast31, 0xc, 0xf, false); });
+        }
+    } else {
+        const int ls = lane & (seg - 1);
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            if (seg > 1) { T y = dpp_row_shr<1>(x[j]); if (ls >= 1) x[j] += y; }
+            if (seg > 2) { T y = dpp_row_shr<2>(x[j]); if (ls >= 2) x[j] += y; }
+            if (seg > 4) { T y = dpp_row_shr<4>(x[j]); if (ls >= 4) x[j] += y; }
+        }
     }
-    if (seg > 32) {
-        // rows 2 and 3 receive lane 31
-        x += per_word(x, [](int w) { return __builtin_amdgcn_update_dpp(0, w, kDppRowBcast31, 0xc, 0xf, false); });
-    }
-    return x;
 }
 
 // ds_swizzle in bit-mask mode within 32-lane halves: source lane =
@@ -242,21 +261,31 @@ __device__ __forceinline__ T swz(T v) {
     return per_word(v, [](int w) { return __builtin_amdgcn_ds_swizzle(w, (AND & 31) | ((OR & 31) << 5)); });
 }
 
-// Inclusive scan over aligned segments of SEG lanes, Ladner-Fischer shape
-// (minimum depth: at step d every lane of the upper half of each 2d-block
-// adds the last value of the lower half, fetched by a swizzle broadcast).
-template <typename T>
-__device__ __forceinline__ T lanes_scan_lf(T x, int seg, int lane) {
-    if (seg > 1) { T y = swz<0x1e, 0x00>(x); if (lane & 1) x += y; }
-    if (seg > 2) { T y = swz<0x1c, 0x01>(x); if (lane & 2) x += y; }
-    if (seg > 4) { T y = swz<0x18, 0x03>(x); if (lane & 4) x += y; }
-    if (seg > 8) { T y = swz<0x10, 0x07>(x); if (lane & 8) x += y; }
-    if (seg > 16) { T y = swz<0x00, 0x0f>(x); if (lane & 16) x += y; }
-    if (seg > 32) {
-        T y = per_word(x, [](int w) { return __builtin_amdgcn_readlane(w, 31); });
-        if (lane & 32) x += y;
+// The same scans, Ladner-Fischer shape (minimum depth: at step d every lane
+// of the upper half of each 2d-block adds the last value of the lower half,
+// fetched by a swizzle broadcast).
+template <typename T, int R>
+__device__ __forceinline__ void lanes_scan_lf(T (&x)[R], int seg, int lane) {
+#define PPX_LF_STEP(D, AND)                            \
+    if (seg > D) {                                     \
+        _Pragma("unroll") for (int j = 0; j < R; ++j) { \
+            const T y = swz<AND, D - 1>(x[j]);         \
+            if (lane & D) x[j] += y;                   \
+        }                                              \
     }
-    return x;
+    PPX_LF_STEP(1, 0x1e)
+    PPX_LF_STEP(2, 0x1c)
+    PPX_LF_STEP(4, 0x18)
+    PPX_LF_STEP(8, 0x10)
+    PPX_LF_STEP(16, 0x00)
+#undef PPX_LF_STEP
+    if (seg > 32) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const T y = per_word(x[j], [](int w) { return __builtin_amdgcn_readlane(w, 31); });
+            if (lane & 32) x[j] += y;
+        }
+    }
 }
 
 }  // namespace ppx
