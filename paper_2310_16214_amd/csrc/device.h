@@ -206,6 +206,14 @@ __device__ __forceinline__ T dpp_wave_shr1(T v) {
     return per_word(v, [](int x) { return __builtin_amdgcn_update_dpp(0, x, kDppWaveShr1, 0xf, 0xf, false); });
 }
 
+// Value of lane (lane + 1) across the whole wave (DPP wave_shl:1); lane 63
+// receives 0, and so does a lane whose neighbour is not active.
+constexpr int kDppWaveShl1 = 0x130;
+template <typename T>
+__device__ __forceinline__ T dpp_wave_shl1(T v) {
+    return per_word(v, [](int x) { return __builtin_amdgcn_update_dpp(0, x, kDppWaveShl1, 0xf, 0xf, false); });
+}
+
 // Value of lane (lane - D) within the same 16-lane row, 0 where that lane is
 // outside the row.
 template <int D, typename T>

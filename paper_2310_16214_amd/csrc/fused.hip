@@ -37,10 +37,10 @@ int64_t mix_lds_bytes(int fam) {
         case kFamTriW64: return 4 * 3 * 64 * 4 * 8;  // per wave: PCR exchange (3 * 64 * 4) or P = 8 staging (64 * 8) doubles
         case kFamTriW64H: return 4 * 64 * 16 * 8;    // per wave: P = 16 staging (64 * 16 doubles) or PCR exchange (3 * 64 * 4)
         case kFamTriLds: return kMixTriLdsBudget;
-        case kFamTriBlk32:
-        case kFamTriBlk32H: return 6 * 1024 * 4;  // two sets of a, c, d lane slots
-        case kFamTriBlk64: return 6 * 1024 * 8;
-        case kFamTriBlk64H: return 6 * 512 * 8;
+        case kFamTriBlk32: return 6 * 1024 * 4;  // two sets of a, c, d lane slots
+        case kFamTriBlk32H: return 17 * 1024 * 4;  // P = 16: the staging buffer and the last exchange's slots
+        case kFamTriBlk64: return 9 * 1024 * 8;    // P = 8: the same
+        case kFamTriBlk64H: return 17 * 512 * 8;   // P = 16: the same
         default: return 0;  // scan: static wave-total slots only
     }
 }

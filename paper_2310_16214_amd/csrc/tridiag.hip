@@ -15,7 +15,7 @@ int64_t tridiag_lds_bytes(int n, const ppx_config &c, int dtype) {
     const int64_t es = dtype == PPX_F64 ? 8 : 4;
     const int64_t P = c.elems_per_thread > 0 ? c.elems_per_thread
                                              : (int64_t)n * c.problems_per_block / c.threads_per_block;
-    if (tri_blk(c.algo, n, P)) return 6 * (int64_t)c.threads_per_block * es;  // two sets of a, c, d slots
+    if (tri_blk(c.algo, n, P)) return tri_blk_lds_vals((int)es, P, c.threads_per_block) * es;
     if (tri_in_wave(c.algo)) {
         // per wave: the PCR_REG exchange buffer (3 * 64 * min(P, 4) values)
         // and the staging buffer of solution chunks of 64 bytes or more

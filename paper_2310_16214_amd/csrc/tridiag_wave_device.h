@@ -103,39 +103,64 @@ __device__ __forceinline__ void wave_store(T *dst, const T (&v)[P]) {
 
 // CR forward levels inside the lane (2s <= P, and 2s <= n/4 so that the last
 // level leaves two equations): equation r = 2s*m + 2s - 1 eliminates r - s and
-// r + s; only the right neighbour of the lane's last active equation can be
-// equation s - 1 of the next lane (one shuffle of three values).  After them
-// each lane's last equation couples the last equations of the lanes beside it.
+// r + s.  Only the lane's last equation P - 1 has a neighbour outside the
+// lane: at the level of stride s, equation s - 1 of the next lane.  That
+// equation is final after the levels below s, and those levels never read
+// equation P - 1, so the levels of all other equations run first
+// (cr_inlane_local), the log2 P neighbour equations of every level are
+// fetched together, and the last equation then goes through its levels
+// (cr_inlane_last): the same eliminations, with one exchange between lanes
+// instead of one per level.
+template <typename T, int P>
+__device__ __forceinline__ void cr_inlane_local(T (&a)[P], T (&c)[P], T (&d)[P]) {
+#pragma unroll
+    for (int s = 1; 2 * s < P; s *= 2)
+#pragma unroll
+        for (int r = 2 * s - 1; r < P - 1; r += 2 * s)
+            unit_eliminate(a[r], c[r], d[r], a[r - s], c[r - s], d[r - s], a[r + s], c[r + s], d[r + s]);
+}
+
+// na[k], nc[k], nd[k]: equation 2^k - 1 of the next lane (zeros past the
+// system), k < log2 P.
+template <int P>
+constexpr int cr_levels() { return P == 2 ? 1 : P == 4 ? 2 : P == 8 ? 3 : 4; }
+template <typename T, int P>
+__device__ __forceinline__ void cr_inlane_last(T (&a)[P], T (&c)[P], T (&d)[P], const T (&na)[cr_levels<P>()],
+                                               const T (&nc)[cr_levels<P>()], const T (&nd)[cr_levels<P>()], int n) {
+#pragma unroll
+    for (int k = 0; k < cr_levels<P>(); ++k) {
+        const int s = 1 << k;
+        if (2 * s <= n / 2)  // the last level leaves two equations
+            unit_eliminate(a[P - 1], c[P - 1], d[P - 1], a[P - 1 - s], c[P - 1 - s], d[P - 1 - s], na[k], nc[k], nd[k]);
+    }
+}
+
 template <typename T, int P>
 __device__ __forceinline__ void cr_inlane_forward(T (&a)[P], T (&c)[P], T (&d)[P], int t, int lps) {
-    const int n = P * lps;
+    cr_inlane_local<T, P>(a, c, d);
     const bool last_lane = t + 1 == lps;
+    constexpr int K = cr_levels<P>();
+    T na[K], nc[K], nd[K];
 #pragma unroll
-    for (int s = 1; 2 * s <= P; s *= 2) {
-        if (2 * s > n / 2) break;  // the last level leaves two equations
-        // equation s - 1 of the next lane: right neighbour of equation P - 1
-        T na = shfl_down(a[s - 1], 1), nc = shfl_down(c[s - 1], 1), nd = shfl_down(d[s - 1], 1);
-        if (last_lane) na = nc = nd = T(0);
-#pragma unroll
-        for (int r = 2 * s - 1; r < P; r += 2 * s) {
-            const bool local = r + s < P;
-            unit_eliminate(a[r], c[r], d[r], a[r - s], c[r - s], d[r - s], local ? a[(r + s) % P] : na,
-                           local ? c[(r + s) % P] : nc, local ? d[(r + s) % P] : nd);
-        }
+    for (int k = 0; k < K; ++k) {
+        const int e = (1 << k) - 1;
+        na[k] = dpp_wave_shl1(a[e]);
+        nc[k] = dpp_wave_shl1(c[e]);
+        nd[k] = dpp_wave_shl1(d[e]);
+        if (last_lane) na[k] = nc[k] = nd[k] = T(0);
     }
+    cr_inlane_last<T, P>(a, c, d, na, nc, nd, P * lps);
 }
 
 // CR back substitution inside the lane (s < P), once every lane's last
 // unknown is in d[P - 1]: equation r = 2s*m + s - 1 gets x_r = d_r - a_r
 // x_{r-s} - c_r x_{r+s}, where x_{r-s} for the lane's first such equation is
-// the previous lane's last unknown.
+// the previous lane's last unknown xl (of no effect in the first lane).
 template <typename T, int P>
-__device__ __forceinline__ void cr_inlane_backward(T (&a)[P], T (&c)[P], T (&d)[P], int t, int lps) {
-    const int n = P * lps;
+__device__ __forceinline__ void cr_inlane_backward(T (&a)[P], T (&c)[P], T (&d)[P], T xl, int t, int n) {
 #pragma unroll
     for (int s = P / 2; s >= 1; s /= 2) {
         if (2 * s > n / 2) continue;
-        const T xl = shfl_up(d[P - 1], 1);  // x of the previous lane's last equation
 #pragma unroll
         for (int r = s - 1; r < P; r += 2 * s) {
             T x = d[r];
@@ -199,7 +224,7 @@ __device__ __forceinline__ void wave_cr(T (&a)[P], T (&c)[P], T (&d)[P], int t, 
             d[P - 1] = x;
         }
     }
-    cr_inlane_backward<T, P>(a, c, d, t, lps);
+    cr_inlane_backward<T, P>(a, c, d, dpp_wave_shr1(d[P - 1]), t, P * lps);
 }
 
 // CR -> PCR hybrid (PPX_TRI_CR_PCR): the CR levels inside the lane reduce
@@ -226,7 +251,7 @@ __device__ __forceinline__ void wave_cr_pcr(T (&a)[P], T (&c)[P], T (&d)[P], int
             unit_eliminate(a[P - 1], c[P - 1], d[P - 1], la, lc, ld, ra, rc, rd);
         }
     }
-    cr_inlane_backward<T, P>(a, c, d, t, lps);
+    cr_inlane_backward<T, P>(a, c, d, dpp_wave_shr1(d[P - 1]), t, P * lps);
 }
 
 // PCR steps with stride S < P, unrolled: the left neighbours of equations
@@ -733,19 +758,42 @@ __device__ __forceinline__ void tridiag_wave_block(const T *A, const T *B, const
 // (PPX_TRI_CR_PCR with 64 < n / P <= 1024)
 //
 // The same three phases as wave_cr_pcr, one system per n / P consecutive
-// threads of the workgroup, but the lanes of a system cross waves, so every
-// exchange between lanes goes through LDS slots indexed by the thread (xs:
+// threads of the workgroup, but the lanes of a system cross waves, so the
+// exchanges between lanes go through LDS slots indexed by the thread (xs:
 // two sets of three arrays of L values, L = the workgroup's threads).  Each
 // exchange writes one set, waits at a barrier and reads it; consecutive
 // exchanges alternate sets, so a set is rewritten only after the barrier of
 // the exchange in between, which every thread reaches after its reads of the
 // set.  An absent neighbour (outside the system) is an identity row (zeros).
-// Barriers: log2 P forward levels, log2(n / P) PCR steps, one for the
-// previous lane's unknown.  Every thread of the workgroup reaches each of
-// them (threads of absent systems solve identity rows).
+//
+// What bounds the longer systems is this chain of barriers, with one to a few
+// workgroups per CU to hide it, so it is kept short: the in-lane levels take
+// one exchange (cr_inlane_last; lanes within a wave by DPP, LDS only from a
+// wave's first lane to the previous wave's last), and PCR takes two steps per
+// exchange, each thread repeating its two neighbours' first step from the six
+// rows around it (four eliminations for two steps instead of two, on one
+// equation per lane against the 2 (P - 1) of the lane's own).  Barriers per
+// system: 2 + ceil(log2(n / P) / 2), against 1 + log2 P + log2(n / P) with an
+// exchange per level and step (7 against 15 for n = 16384, P = 16).  With the
+// staged stores, 2^23 float32 unknowns at n = 16384 take 39.2 us (49.2 before,
+// both at P = 16), 2^22 float64 unknowns at n = 8192 44.8 (51.9, P = 8), 777
+// float64 systems of 4096 27.0 (32.9); a copy of the same five arrays takes
+// 31 us for 160 MiB.  Every
+// thread of the workgroup reaches each of them (threads of absent systems
+// solve identity rows).  last: L values for the last exchange, outside both
+// sets where the caller goes on to use their space.
+template <typename T>
+struct TriRow {
+    T a, c, d;
+};
+template <typename T>
+__device__ __forceinline__ TriRow<T> row_eliminate(TriRow<T> r, const TriRow<T> &l, const TriRow<T> &u) {
+    unit_eliminate(r.a, r.c, r.d, l.a, l.c, l.d, u.a, u.c, u.d);
+    return r;
+}
 template <typename T, int P>
 __device__ __forceinline__ void block_cr_pcr(T (&a)[P], T (&c)[P], T (&d)[P], int t, int lps, int tx, int L,
-                                             T *xs) {
+                                             T *xs, T *last) {
     int set = 0;
     auto slots = [&]() {
         T *w = xs + (set & 1) * 3 * L;
@@ -753,67 +801,92 @@ __device__ __forceinline__ void block_cr_pcr(T (&a)[P], T (&c)[P], T (&d)[P], in
         return w;
     };
     // ---- CR forward levels inside the lane
-#pragma unroll
-    for (int s = 1; 2 * s <= P; s *= 2) {
+    cr_inlane_local<T, P>(a, c, d);
+    {
+        constexpr int K = cr_levels<P>();
+        T na[K], nc[K], nd[K];
         T *w = slots();
-        w[tx] = a[s - 1];
-        w[L + tx] = c[s - 1];
-        w[2 * L + tx] = d[s - 1];
-        __syncthreads();
-        T na = T(0), nc = T(0), nd = T(0);  // equation s - 1 of the next lane
-        if (t + 1 < lps) {
-            na = w[tx + 1];
-            nc = w[L + tx + 1];
-            nd = w[2 * L + tx + 1];
-        }
+        const int lane = tx & 63, wave = tx >> 6;
+        if (lane == 0) {
 #pragma unroll
-        for (int r = 2 * s - 1; r < P; r += 2 * s) {
-            const bool local = r + s < P;
-            unit_eliminate(a[r], c[r], d[r], a[r - s], c[r - s], d[r - s], local ? a[(r + s) % P] : na,
-                           local ? c[(r + s) % P] : nc, local ? d[(r + s) % P] : nd);
+            for (int k = 0; k < K; ++k) {
+                const int e = (1 << k) - 1;
+                w[(wave * K + k) * 3] = a[e];
+                w[(wave * K + k) * 3 + 1] = c[e];
+                w[(wave * K + k) * 3 + 2] = d[e];
+            }
         }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int e = (1 << k) - 1;
+            na[k] = dpp_wave_shl1(a[e]);
+            nc[k] = dpp_wave_shl1(c[e]);
+            nd[k] = dpp_wave_shl1(d[e]);
+        }
+        if (t + 1 == lps) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) na[k] = nc[k] = nd[k] = T(0);
+        } else if (lane == 63) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                na[k] = w[((wave + 1) * K + k) * 3];
+                nc[k] = w[((wave + 1) * K + k) * 3 + 1];
+                nd[k] = w[((wave + 1) * K + k) * 3 + 2];
+            }
+        }
+        cr_inlane_last<T, P>(a, c, d, na, nc, nd, P * lps);
     }
     // ---- PCR on the lanes' last equations
-    for (int dl = 1; dl < lps; dl *= 2) {
+    TriRow<T> r{a[P - 1], c[P - 1], d[P - 1]};
+    const auto row = [&](const T *w, int o) {  // the row o lanes away (zeros outside the system)
+        TriRow<T> v{T(0), T(0), T(0)};
+        if ((unsigned)(t + o) < (unsigned)lps) v = {w[tx + o], w[L + tx + o], w[2 * L + tx + o]};
+        return v;
+    };
+    const auto publish = [&]() {
         T *w = slots();
-        w[tx] = a[P - 1];
-        w[L + tx] = c[P - 1];
-        w[2 * L + tx] = d[P - 1];
+        w[tx] = r.a;
+        w[L + tx] = r.c;
+        w[2 * L + tx] = r.d;
         __syncthreads();
-        T la = T(0), lc = T(0), ld = T(0), ra = T(0), rc = T(0), rd = T(0);
-        if (t >= dl) {
-            la = w[tx - dl];
-            lc = w[L + tx - dl];
-            ld = w[2 * L + tx - dl];
-        }
-        if (t + dl < lps) {
-            ra = w[tx + dl];
-            rc = w[L + tx + dl];
-            rd = w[2 * L + tx + dl];
-        }
-        unit_eliminate(a[P - 1], c[P - 1], d[P - 1], la, lc, ld, ra, rc, rd);
+        return w;
+    };
+    int dl = 1;
+    if (__builtin_ctz(lps) & 1) {  // an odd number of steps: one by itself
+        const T *w = publish();
+        r = row_eliminate(r, row(w, -1), row(w, 1));
+        dl = 2;
     }
+    for (; dl < lps; dl *= 4) {  // steps dl and 2 dl
+        const T *w = publish();
+        const TriRow<T> l1 = row(w, -dl), u1 = row(w, dl);
+        TriRow<T> l2 = row_eliminate(row(w, -2 * dl), row(w, -3 * dl), l1);
+        TriRow<T> u2 = row_eliminate(row(w, 2 * dl), u1, row(w, 3 * dl));
+        if (t < 2 * dl) l2 = {T(0), T(0), T(0)};
+        if (t + 2 * dl >= lps) u2 = {T(0), T(0), T(0)};
+        r = row_eliminate(row_eliminate(r, l1, u1), l2, u2);
+    }
+    d[P - 1] = r.d;
     // ---- the previous lane's last unknown, then back substitution in the lane
-    T *w = slots();
-    w[tx] = d[P - 1];
+    last[tx] = r.d;
     __syncthreads();
-    const T xl = t > 0 ? w[tx - 1] : T(0);
-#pragma unroll
-    for (int s = P / 2; s >= 1; s /= 2) {
-#pragma unroll
-        for (int r = s - 1; r < P; r += 2 * s) {
-            T x = d[r];
-            if (r >= s) x -= a[r] * d[r - s];
-            else x -= a[r] * xl;  // xl = 0 in the first lane, where a[0] = 0 too
-            x -= c[r] * d[r + s];
-            d[r] = x;
-        }
-    }
+    cr_inlane_backward<T, P>(a, c, d, t > 0 ? last[tx - 1] : T(0), t, P * lps);
+}
+
+// LDS values of a workgroup of L threads: the two slot sets, or, where the
+// solution leaves through the staging buffer (tri_staged_stores), the larger
+// of the sets and the buffer (the sets are read before the last exchange's
+// barrier, the buffer written after it), and the last exchange's slots beside.
+template <typename T, int P>
+constexpr bool tri_blk_staged() { return P * (int)sizeof(T) >= 64; }
+constexpr int64_t tri_blk_lds_vals(int elem_bytes, int64_t P, int64_t L) {
+    return P * elem_bytes >= 64 ? ((P > 6 ? P : 6) + 1) * L : 6 * L;
 }
 
 // One workgroup's share of the multi-wave hybrid: systems [first, first +
 // nsys), lps = n / P > 64 lanes each (several waves), L = the workgroup's
-// threads (a multiple of lps); xs holds 6 * L values.
+// threads (a multiple of lps); xs holds tri_blk_lds_vals values.
 template <typename T, int P>
 __device__ __forceinline__ void tridiag_blk_block(const T *A, const T *B, const T *C, const T *D, T *X,
                                                   int log2n, long long first, int nsys, T *xs, int tx, int L) {
@@ -845,14 +918,24 @@ __device__ __forceinline__ void tridiag_blk_block(const T *A, const T *B, const 
         c[j] *= r;
         d[j] *= r;
     }
-    block_cr_pcr<T, P>(a, c, d, t, lps, tx, L, xs);
-    if (active) wave_store<T, P>(X + base, d);
+    if constexpr (tri_blk_staged<T, P>()) {
+        block_cr_pcr<T, P>(a, c, d, t, lps, tx, L, xs, xs + (P > 6 ? P : 6) * L);
+        const int w0 = tx & ~63;
+        wave_store_staged<T, P>(X + first * n + (long long)w0 * P, d, xs + w0 * P, tx & 63,
+                                max(0, min(64, nsys * lps - w0)));
+    } else {
+        // the last exchange may take either set: the one of the exchange
+        // before it is still being read
+        const int exchanges = 1 + (__builtin_ctz(lps) + 1) / 2;
+        block_cr_pcr<T, P>(a, c, d, t, lps, tx, L, xs, xs + (exchanges & 1) * 3 * L);
+        if (active) wave_store<T, P>(X + base, d);
+    }
 }
 
 template <typename T, int P>
 __global__ __launch_bounds__(tri_blk_max_threads(sizeof(T), P)) void k_tridiag_blk(const T *a, const T *b, const T *c, const T *d, T *x,
                                                       int log2n, long long batch, int gb) {
-    extern __shared__ float4 smem_raw[];  // 6 * blockDim.x values
+    extern __shared__ float4 smem_raw[];  // tri_blk_lds_vals
     const long long first = (long long)blockIdx.x * gb;
     const int nsys = (int)min((long long)gb, batch - first);
     tridiag_blk_block<T, P>(a, b, c, d, x, log2n, first, nsys, reinterpret_cast<T *>(smem_raw), threadIdx.x,
