@@ -360,6 +360,12 @@ int mix_prepare_kernels() {
             }
         }
     }
+    for (int c = 0; c < kMixClasses; ++c) {
+        int64_t lds = 0;
+        for (int f = 0; f < kMixFamilies; ++f)
+            if (kMixClassMask[c] & (1 << f)) lds = std::max(lds, mix_lds_bytes(f));
+        (void)hipFuncSetAttribute(mix_class_kernel(c), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    }
     g_prepared = true;
     return PPX_OK;
 }
@@ -383,7 +389,7 @@ int mix_enqueue(char *d_tables, int mask, const int64_t *ntiles, const unsigned 
                            dim3(block), mix_lds_at(f, block), s, a, tw);
         e = hipGetLastError();
         if (e == hipSuccess && after)
-            if (int rc = after(arg, f, s)) return rc;
+            if (int rc = after(arg, 1 << f, s)) return rc;
     }
     return fail_hip(e, "mixed launch");
 }
@@ -414,50 +420,125 @@ bool mix_args_fit(const char *table, int mask) {
 // four per CU (one per SIMD).
 constexpr int kMixFillPerCu = 4;
 
+// The families of class c whose tiles share the class kernel in a launch:
+// fewest tiles first, as long as together they come to at most three (small)
+// or two (large) workgroups of the class's size per CU.  Families that small
+// leave most of the GPU idle in a kernel of their own, and their kernels'
+// ramps and tails add up: 16 jobs of the serving mix (9.1 M elements) take
+// 40 us against 53 in one kernel per family, 8 jobs with one of every large
+// kind 31.6 against 56.  A family beyond that fills the GPU by itself, at its
+// own occupancy: with no limit, 48 jobs (28-35 M elements) took 155-189 us
+// against 118-156, with the limits 100-136; a limit of ten for the small
+// class costs 16 jobs up to 1.3x, one of one for the large class up to 1.2x.
+static int mix_class_families(int c, int mask, const int64_t *tiles, const int *jobs, int cus) {
+    const int64_t cap = (int64_t)cus * (c == kClassSmall ? 3 : 2);
+    int picked = 0, njobs = 0;
+    int64_t total = 0;
+    for (;;) {
+        int best = -1;
+        for (int f = 0; f < kMixFamilies; ++f)
+            if ((mask & kMixClassMask[c] & ~picked & (1 << f)) && (best < 0 || tiles[f] < tiles[best])) best = f;
+        if (best < 0 || total + tiles[best] > cap || njobs + jobs[best] > kMixClassJobs) break;
+        picked |= 1 << best;
+        total += tiles[best];
+        njobs += jobs[best];
+    }
+    return __builtin_popcount((unsigned)picked) > 1 ? picked : 0;
+}
+
 int mix_enqueue_args(const char *table, int mask, const int *order, int norder, const float2 *tw, hipStream_t s,
                      mix_after_family_t after, void *arg) {
     const MixHeader *h = reinterpret_cast<const MixHeader *>(table);
     const MixJob *rec = reinterpret_cast<const MixJob *>(table + kMixHeaderBytes);
+    const int cus = device_info()->cus;
     // A launch with fewer full tiles than it takes to fill the GPU runs its
     // families in smaller workgroups (a problem's threads and arithmetic
     // unchanged, fewer problems per tile), which spreads small batches over
     // more CUs; the LDS-exchange tridiagonal family keeps its shape.
     int64_t total = 0;
+    int jobs_of[kMixFamilies] = {};
     for (int f = 0; f < kMixFamilies; ++f)
         if (mask & (1 << f)) total += h->ntiles[f];
-    const int64_t fill = (int64_t)kMixFillPerCu * device_info()->cus;
+    for (unsigned i = 0; i < h->njobs; ++i) ++jobs_of[rec[i].family];
+    const int64_t fill = (int64_t)kMixFillPerCu * cus;
     int shrink = 1;
     while (shrink < 1024 && total * shrink * 2 <= fill) shrink *= 2;
+    // the families that share each class's kernel
+    int shared[kMixClasses];
+    for (int c = 0; c < kMixClasses; ++c) {
+        int64_t tiles[kMixFamilies];
+        for (int f = 0; f < kMixFamilies; ++f) {
+            const int64_t threads = (int64_t)h->ntiles[f] * h->block[f];
+            tiles[f] = (threads + mix_class_block(c) - 1) / mix_class_block(c);
+        }
+        shared[c] = mix_class_families(c, mask, tiles, jobs_of, cus);
+    }
+    // Records of the families in `fams` at workgroup size `block`, appended
+    // family by family in the order given, first_tile ascending (as the
+    // kernels scan them).
+    const auto records = [&](int fams, const int *by, int nby, int block, MixJob *out, unsigned *ntiles) {
+        unsigned n = 0;
+        *ntiles = 0;
+        for (int o = 0; o < nby; ++o)
+            for (unsigned i = 0; i < h->njobs; ++i) {
+                if (rec[i].family != by[o] || !(fams & (1 << by[o]))) continue;
+                MixJob r = rec[i];
+                r.per_tile = (int)((int64_t)r.per_tile * block / (int)h->block[by[o]]);
+                r.first_tile = *ntiles;
+                *ntiles += (unsigned)((r.batch + r.per_tile - 1) / r.per_tile);
+                out[n++] = r;
+            }
+        return n;
+    };
+    // threads of the widest problem among the families' jobs (at least a wave)
+    const auto widest = [&](int fams) {
+        int need = kWave;
+        for (unsigned i = 0; i < h->njobs; ++i)
+            if (fams & (1 << rec[i].family)) need = std::max(need, (int)h->block[rec[i].family] / rec[i].per_tile);
+        return need;
+    };
     hipError_t e = hipSuccess;
+    int done = 0;
     for (int o = 0; o < norder && e == hipSuccess; ++o) {
         const int f = order[o];
-        if (!(mask & (1 << f))) continue;
-        const int full = (int)h->block[f];
-        int block = full;
-        if (shrink > 1 && f != kFamTriLds) {
-            int need = kWave;  // threads of the widest problem among the family's jobs
-            for (unsigned i = 0; i < h->njobs; ++i)
-                if (rec[i].family == f) need = std::max(need, full / rec[i].per_tile);
-            block = std::max(full / shrink, need);
+        if (!(mask & (1 << f)) || (done & (1 << f))) continue;
+        int fams = 1 << f, c = -1;
+        for (int q = 0; q < kMixClasses; ++q)
+            if (shared[q] & (1 << f)) c = q;
+        if (c >= 0) {
+            // a class goes when its last family's turn comes (the order is by work)
+            fams = shared[c];
+            bool later = false;
+            for (int q = o + 1; q < norder; ++q) later = later || (fams & (1 << order[q]));
+            if (later) continue;
+            const int full = mix_class_block(c);
+            const int block = shrink > 1 ? std::max(full / shrink, widest(fams)) : full;
+            // the families with the longest tiles first, so that none of
+            // those is the last to start
+            static constexpr int by[kMixClasses][5] = {
+                {kFamTriW32H, kFamFft256, kFamTriW32, kFamScan256, -1},
+                {kFamFft1024, kFamTriBlk32H, kFamFft1024P8, kFamTriBlk32, kFamScan1024}};
+            MixClassArgs a;
+            a.tw = tw;
+            a.njobs = records(fams, by[c], c == kClassSmall ? 4 : 5, block, a.jobs, &a.ntiles);
+            size_t lds = 0;
+            for (int q = 0; q < kMixFamilies; ++q)
+                if (fams & (1 << q)) lds = std::max(lds, mix_lds_at(q, block));
+            hipLaunchKernelGGL(reinterpret_cast<mix_class_kernel_t>(const_cast<void *>(mix_class_kernel(c))),
+                               dim3(a.ntiles), dim3(block), lds, s, a);
+        } else {
+            const int full = (int)h->block[f];
+            const int block = shrink > 1 && f != kFamTriLds ? std::max(full / shrink, widest(fams)) : full;
+            MixArgs a;
+            a.tables = nullptr;
+            a.njobs = records(fams, &f, 1, block, a.jobs, &a.ntiles);
+            hipLaunchKernelGGL(reinterpret_cast<mix_kernel_t>(const_cast<void *>(mix_kernel(f, true))),
+                               dim3(a.ntiles), dim3(block), mix_lds_at(f, block), s, a, tw);
         }
-        MixArgs a;
-        a.tables = nullptr;
-        a.ntiles = 0;
-        a.njobs = 0;
-        for (unsigned i = 0; i < h->njobs; ++i) {
-            if (rec[i].family != f) continue;
-            MixJob r = rec[i];  // first_tile ascending, as the kernel scans them
-            r.per_tile = (int)((int64_t)r.per_tile * block / full);
-            r.first_tile = a.ntiles;
-            a.ntiles += (unsigned)((r.batch + r.per_tile - 1) / r.per_tile);
-            a.jobs[a.njobs++] = r;
-        }
-        const size_t lds = mix_lds_at(f, block);
-        hipLaunchKernelGGL(reinterpret_cast<mix_kernel_t>(const_cast<void *>(mix_kernel(f, true))), dim3(a.ntiles),
-                           dim3(block), lds, s, a, tw);
+        done |= fams;
         e = hipGetLastError();
         if (e == hipSuccess && after)
-            if (int rc = after(arg, f, s)) return rc;
+            if (int rc = after(arg, fams, s)) return rc;
     }
     return fail_hip(e, "mixed launch");
 }
@@ -471,10 +552,10 @@ struct StageCtx {
     unsigned nrec;
     int next;
 };
-int after_family(void *arg, int fam, hipStream_t s) {
+int after_family(void *arg, int families, hipStream_t s) {
     auto *c = static_cast<StageCtx *>(arg);
     for (unsigned r = 0; r < c->nrec; ++r)
-        if (c->rec[r].family == fam) c->hook->job_stage[c->rec_job[r]] = c->next;
+        if (families & (1 << c->rec[r].family)) c->hook->job_stage[c->rec_job[r]] = c->next;
     ++c->next;
     return c->hook->stage(c->hook->arg, s);
 }

@@ -137,6 +137,24 @@ struct MixArgs {
 };
 static_assert(sizeof(MixArgs) <= 4096 - 64, "kernel arguments are limited to 4 KiB");
 
+// Classes of families that share a kernel in an argument launch
+// (mixed_class.hip), their workgroup sizes, and what their kernels are
+// launched with.
+enum MixClass : int { kClassSmall = 0, kClassLarge, kMixClasses };
+constexpr int kMixClassMask[kMixClasses] = {
+    1 << kFamFft256 | 1 << kFamScan256 | 1 << kFamTriW32 | 1 << kFamTriW32H,
+    1 << kFamFft1024 | 1 << kFamFft1024P8 | 1 << kFamScan1024 | 1 << kFamTriBlk32 | 1 << kFamTriBlk32H};
+constexpr int mix_class_block(int cls) { return cls == kClassSmall ? 256 : 1024; }
+constexpr int kMixClassJobs = 54;
+struct MixClassArgs {
+    const float2 *tw;
+    unsigned ntiles, njobs;
+    MixJob jobs[kMixClassJobs];
+};
+static_assert(sizeof(MixClassArgs) <= 4096 - 64, "kernel arguments are limited to 4 KiB");
+typedef void (*mix_class_kernel_t)(MixClassArgs a);
+const void *mix_class_kernel(int cls);
+
 // Kernel of a family (signature mix_kernel_t), persistent or taking its
 // records in the arguments, from the translation unit that instantiates it.
 typedef void (*mix_kernel_t)(MixArgs a, const float2 *tw);
@@ -186,8 +204,9 @@ int mix_build_tables(const ppx_job *jobs, int njobs, char *buf, int64_t *ntiles_
 // their jobs, so that the families of small jobs finish first.  Returns
 // their count.
 int mix_family_order(const char *table, int mask, int *order);
-// Called after each family kernel is enqueued (may be empty).
-typedef int (*mix_after_family_t)(void *arg, int fam, hipStream_t s);
+// Called after each kernel is enqueued, with the mask of the families whose
+// tiles it runs (may be empty).
+typedef int (*mix_after_family_t)(void *arg, int families, hipStream_t s);
 // Launches job j alone with configuration c (a direct job).
 int mix_launch_direct(const ppx_job &j, const ppx_config &c, hipStream_t s);
 // Occupancy of every family kernel on the current device (once).
@@ -199,7 +218,8 @@ int mix_enqueue(char *d_tables, int mask, const int64_t *ntiles, const unsigned 
                 const float2 *tw, hipStream_t s, mix_after_family_t after = nullptr, void *arg = nullptr);
 // Whether the launch planned in `table` (header and records) can pass its
 // jobs as kernel arguments (at most kMixArgJobs per family), and if so its
-// launches: one argument kernel per family in mask, a workgroup per tile.
+// launches: one argument kernel per family in mask, or per class of families
+// where that pays (mix_class_families in fused.hip), a workgroup per tile.
 // A launch too small to fill the GPU runs smaller workgroups (fewer
 // problems per tile, never fewer threads than a problem or a wave needs).
 bool mix_args_fit(const char *table, int mask);

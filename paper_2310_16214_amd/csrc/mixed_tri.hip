@@ -8,51 +8,23 @@
 // 56-62 for CR, WM and LF) would otherwise halve the others' occupancy.
 // Larger systems run the LDS CR or PCR in 1024-thread workgroups with
 // 128 KiB of LDS.
-#include "mixed.h"
+#include "mixed_dispatch.h"
 #include "tridiag_device.h"
-#include "tridiag_wave_device.h"
 
 namespace ppx {
 
-template <int FAM>
-using TriwType = typename std::conditional<FAM == kFamTriW32 || FAM == kFamTriW32H, float, double>::type;
-// Whether the family FAM holds the in-wave shape (ALGO, P).
-template <int FAM>
-constexpr bool triw_member(int algo, int P) {
-    return mix_triw_family(FAM == kFamTriW64 || FAM == kFamTriW64H, algo, P) == FAM;
-}
-
-template <int FAM, int ID>
-__device__ __forceinline__ void mix_triw_dispatch(const MixJob &j, long long first, int count, void *smem, int tx) {
-    if constexpr (ID < kMixTriwShapes) {
-        using T = TriwType<FAM>;
-        constexpr int ALGO = PPX_TRI_CR_PCR + ID / 4;
-        constexpr int LP = ID % 4 + 1;
-        constexpr int P = 1 << LP;
-        if constexpr (triw_member<FAM>(ALGO, P)) {
-            static_assert(mix_triw_shape(ALGO, LP) == ID, "shape code");
-            if (j.shape == ID) {
-                tridiag_wave_block<T, ALGO, P>(static_cast<const T *>(j.p[0]), static_cast<const T *>(j.p[1]),
-                                               static_cast<const T *>(j.p[2]), static_cast<const T *>(j.p[3]),
-                                               static_cast<T *>(j.out), j.log2n, first, count,
-                                               static_cast<T *>(smem), tx);
-                return;
-            }
-        }
-        mix_triw_dispatch<FAM, ID + 1>(j, first, count, smem, tx);
-    }
-}
-
 // float64 with 16 equations per lane: at least three waves per SIMD, as for
-// the single-call kernels of those shapes (tri_wave_min_waves).
+// the single-call kernels of those shapes (tri_wave_min_waves); the other
+// families with PCR shapes: four (left alone they take 129 and 132 VGPRs,
+// just over what four waves have).
 template <int FAM>
-constexpr int triw_min_waves() { return FAM == kFamTriW64H ? 3 : 1; }
+constexpr int triw_min_waves() { return FAM == kFamTriW64H ? 3 : FAM == kFamTriW32 ? 1 : 4; }
 
 template <int FAM, bool ARGS>
 __global__ __launch_bounds__(256, triw_min_waves<FAM>()) void k_mix_triw(MixArgs a, const float2 *) {
     extern __shared__ float4 smem[];  // PPX_TRI_PCR_REG exchange buffers, one per wave
     mix_tile_loop<FAM, ARGS>(a, [&](const MixJob &j, long long first, int count, int tx, int nt) {
-        mix_triw_dispatch<FAM, 0>(j, first, count, smem, tx);
+        mix_triw_dispatch<FAM>(j, first, count, smem, tx);
     });
 }
 
@@ -87,28 +59,6 @@ __global__ __launch_bounds__(1024) void k_mix_tril(MixArgs a, const float2 *) {
                 break;
         }
     });
-}
-
-// The hybrid across waves: a tile is nt / (n / P) systems (nt the workgroup
-// size), the lanes exchanging through LDS slots (two sets of a, c, d per
-// thread).
-template <int FAM, int LP>
-__device__ __forceinline__ void mix_trib_dispatch(const MixJob &j, long long first, int count, void *smem, int tx,
-                                                  int nt) {
-    if constexpr (LP <= 4) {
-        using T = typename std::conditional<FAM == kFamTriBlk32 || FAM == kFamTriBlk32H, float, double>::type;
-        constexpr int P = 1 << LP;
-        if constexpr ((FAM == kFamTriBlk32H || FAM == kFamTriBlk64H) == (P == 16)) {
-            if (j.shape == LP - 1) {
-                tridiag_blk_block<T, P>(static_cast<const T *>(j.p[0]), static_cast<const T *>(j.p[1]),
-                                        static_cast<const T *>(j.p[2]), static_cast<const T *>(j.p[3]),
-                                        static_cast<T *>(j.out), j.log2n, first, count, static_cast<T *>(smem), tx,
-                                        nt);
-                return;
-            }
-        }
-        mix_trib_dispatch<FAM, LP + 1>(j, first, count, smem, tx, nt);
-    }
 }
 
 template <int FAM, bool ARGS>
