@@ -173,4 +173,37 @@ int enumerate_configs(int op, int dtype, int64_t n, ppx_config *out, int cap) {
     return count;
 }
 
+// A tuned shape is the fastest on a full GPU.  A call too small to give every
+// SIMD a wave at the tuned values per thread P is bound by the length of one
+// thread's work instead, and takes half the values per thread (the radix with
+// it) as long as that holds:
+// * FFT, radix = P = 16, n = 1024 or 2048: radix 8.  64 problems of n = 1024
+//   in one wave or two each: 3.90 us at radix 16, 3.49 at radix 8; 1024
+//   problems 6.12 and 5.52; n = 2048, 32 problems 4.44 and 4.04; at 2^22
+//   elements radix 16 is the faster one (12.4 against over 12.9).  At n =
+//   4096 the two are equal, below 1024 the tuned radix is 8 already.
+// * Tridiagonal, the CR -> PCR hybrid, WM and LF inside a wave, down to P = 4
+//   while a system still fits one: float32, n = 256, 64 systems 3.29 us at P =
+//   16, 2.67 at P = 4; 1024 systems 4.18 and 3.69; float64, n = 64, 1024
+//   systems 4.15 at P = 8, 3.07 at P = 4.
+constexpr int64_t kFullGpuWaves = 1024;  // one per SIMD
+void fit_shape(int op, int dtype, int64_t n, int64_t batch, ppx_config &c) {
+    const auto waves = [&] { return n * batch / ((int64_t)c.elems_per_thread * kWave); };
+    const auto halve = [&] {
+        c.elems_per_thread /= 2;
+        if (op == PPX_OP_FFT) c.radix /= 2;
+        if (c.problems_per_block > 1) c.problems_per_block /= 2;
+        else c.threads_per_block *= 2;
+        c.lds_elems = 0;
+        complete_config(op, dtype, n, c);
+    };
+    if (op == PPX_OP_FFT) {
+        if (c.radix == 16 && c.elems_per_thread == 16 && (n == 1024 || n == 2048) && waves() <= kFullGpuWaves) halve();
+    } else if (op == PPX_OP_TRIDIAG) {
+        const int base = tri_base(c.algo);
+        if (base != PPX_TRI_CR_PCR && base != PPX_TRI_WM && base != PPX_TRI_LF) return;
+        while (c.elems_per_thread > 4 && n / c.elems_per_thread * 2 <= kWave && waves() < kFullGpuWaves) halve();
+    }
+}
+
 }  // namespace ppx

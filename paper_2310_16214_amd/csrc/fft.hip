@@ -110,12 +110,21 @@ int launch_fft(const void *in, void *out, int log2n, int64_t batch, const ppx_co
     FftKernel k = fft_lookup(c.radix, c.elems_per_thread, c.algo, log2n);
     if (!k) return fail(PPX_ECONFIG, "no FFT kernel for this radix / elements-per-thread");
     const int n = 1 << log2n;
-    const int64_t lds = fft_lds_bytes(n, c.problems_per_block, c.algo, c.radix);
+    int64_t lds = fft_lds_bytes(n, c.problems_per_block, c.algo, c.radix);
     if (lds > di->lds_per_block) return fail(PPX_ECONFIG, "FFT configuration exceeds the LDS per workgroup");
     int64_t grid = (batch + c.problems_per_block - 1) / c.problems_per_block;
     if (c.algo & PPX_FFT_LDS_PIPE) {  // persistent: at most the resident workgroups
         const int64_t resident = (int64_t)resident_blocks_per_cu(k, c.threads_per_block, lds) * di->cus;
-        if (resident < grid) grid = resident;
+        if (resident < grid) {
+            grid = resident;
+        } else {
+            // every workgroup has one group: nothing to prefetch, so the plain
+            // kernel, which does not copy the twiddle bases to LDS first (one
+            // problem of n = 16384: 11.5 us persistent, 10.5 plain)
+            const int algo = c.algo & ~PPX_FFT_LDS_PIPE;
+            k = fft_lookup(c.radix, c.elems_per_thread, algo, log2n);
+            lds = fft_lds_bytes(n, c.problems_per_block, algo, c.radix);
+        }
     }
     hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(c.threads_per_block), (size_t)lds, s,
                        static_cast<const float2 *>(in), static_cast<float2 *>(out),

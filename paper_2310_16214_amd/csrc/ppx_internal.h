@@ -182,6 +182,9 @@ int launch_mixed_impl(const ppx_job *jobs, int njobs, hipStream_t stream, hipEve
 int validate_config(int op, int dtype, int64_t n, const ppx_config &c);
 void complete_config(int op, int dtype, int64_t n, ppx_config &c);
 int default_config(int op, int dtype, int64_t n, ppx_config &c);
+// The values per thread of a tuned configuration for a batch too small to
+// fill the GPU with it (rule in config.cpp).
+void fit_shape(int op, int dtype, int64_t n, int64_t batch, ppx_config &c);
 int enumerate_configs(int op, int dtype, int64_t n, ppx_config *out, int cap);
 int analytical_config(int op, int dtype, int64_t n, int64_t batch, ppx_config &c);
 // The configuration of a tridiagonal call restricted to one family (tuned

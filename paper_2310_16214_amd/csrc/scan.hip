@@ -98,6 +98,9 @@ int launch_scan(const void *in, void *out, int log2n, int64_t batch, int dtype, 
         if (!di) return PPX_EDEVICE;
         const int64_t resident = (int64_t)scan_resident_per_cu(k, c.threads_per_block) * di->cus;
         if (resident < grid) grid = resident;
+        // every workgroup has one group: nothing to prefetch (16 rows of 4096
+        // float32: 2.64 us persistent, 2.23 plain)
+        else k = scan_kernel(dtype, c.elems_per_thread, c.algo & ~PPX_SCAN_KS_PIPE, exclusive);
     }
     const dim3 g((unsigned)grid), b(c.threads_per_block);
     if (dtype == PPX_I32) launch_t<int>(k, g, b, s, in, out, log2n, batch, c.problems_per_block);

@@ -142,6 +142,8 @@ int launch_tridiag(const void *a, const void *b, const void *c, const void *d, v
     if (cfg.algo & PPX_TRI_PIPE) {  // persistent: at most the resident workgroups
         const int64_t resident = (int64_t)tri_resident_per_cu(k, cfg.threads_per_block, lds) * di->cus;
         if (resident < grid) grid = resident;
+        // every workgroup has one group: nothing to prefetch (the LDS is the same)
+        else k = tridiag_kernel(dtype, cfg.algo & ~PPX_TRI_PIPE, cfg.elems_per_thread, int64_t(1) << log2n);
     }
     if (dtype == PPX_F64) return launch_t<double>(k, a, b, c, d, x, log2n, batch, cfg, (size_t)lds, grid, s);
     return launch_t<float>(k, a, b, c, d, x, log2n, batch, cfg, (size_t)lds, grid, s);
