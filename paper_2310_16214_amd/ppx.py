@@ -95,6 +95,8 @@ def lib():
     HIP runtime and torch's device pointers and streams are valid here.
     """
     global _lib
+    if _lib is not None:  # set once, complete
+        return _lib
     with _lock:
         if _lib is None:
             try:
@@ -147,13 +149,27 @@ def _ptr(x):
     return int(x)
 
 
+_raw_stream = None
+
+
+def _current_stream(device_index=None):
+    """Handle of torch's current HIP stream on a device (the current one if
+    None).  torch.cuda.current_stream() builds a Stream object to hold the
+    handle, 2.2 us of a 6.1 us call; the raw accessor takes 0.1 us."""
+    global _raw_stream
+    import torch
+    if _raw_stream is None:
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream",
+                              lambda i: torch.cuda.current_stream(i).cuda_stream)
+    return _raw_stream(torch.cuda.current_device() if device_index is None else device_index)
+
+
 def _stream(stream, *tensors):
     if stream is not None:
         return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
     for t in tensors:
-        if hasattr(t, "is_cuda") and t.is_cuda:
-            import torch
-            return torch.cuda.current_stream(t.device).cuda_stream
+        if getattr(t, "is_cuda", False):
+            return _current_stream(t.get_device())
     return None
 
 
@@ -566,8 +582,7 @@ def launch_mixed(jobs, stream=None):
         f._ppx_typed = True
     arr = (Job * len(jobs))(*jobs)
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream().cuda_stream
+        stream = _current_stream()
     elif hasattr(stream, "cuda_stream"):
         stream = stream.cuda_stream
     _check(f(arr, len(jobs), stream))
@@ -594,8 +609,7 @@ def launch_mixed_noalloc(jobs, stream=None):
         f._ppx_typed = True
     arr = (Job * len(jobs))(*jobs)
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream().cuda_stream
+        stream = _current_stream()
     elif hasattr(stream, "cuda_stream"):
         stream = stream.cuda_stream
     _check(f(arr, len(jobs), stream))
