@@ -20,7 +20,9 @@
  *   Compute calls are asynchronous and stream-ordered.
  * - `cfg` may be NULL: the library then uses the configuration recorded by
  *   tune() for (op, dtype, n) if there is one, else the analytical model's
- *   choice.  An explicit cfg is validated (ppx_config_valid) and rejected
+ *   choice.  A batch too small to fill the GPU with a recorded configuration
+ *   takes fewer values per thread (ppx_resolve_config says which), and fewer
+ *   problems per workgroup, which changes no result.  An explicit cfg is validated (ppx_config_valid) and rejected
  *   with PPX_ECONFIG if it does not describe a valid launch.
  * - Every call returns PPX_OK (0) or a negative PPX_E* code; a message is
  *   then available from ppx_last_error() (thread-local).  Argument checks run
@@ -183,7 +185,9 @@ typedef struct ppx_fft_plan {
  * fft_batched_large -- same transform and conventions as fft_batched, for
  * PPX_MAX_N < n <= PPX_MAX_N_LARGE.  in and out must not overlap at all (out
  * holds the intermediate between the passes).  plan == NULL: the plan
- * tune_fft_large recorded for n, else ppx_default_fft_plan.  Errors:
+ * tune_fft_large recorded for n, else ppx_default_fft_plan; a batch with
+ * fewer tiles than CUs in one of that plan's passes, and smaller than the one
+ * it was tuned at, takes a plan of shorter columns and narrower tiles.  Errors:
  * PPX_EINVAL (pointers, n, batch, direction, overlap), PPX_ECONFIG (plan).
  * fft_batched with such an n and cfg == NULL forwards here.
  */

@@ -213,7 +213,11 @@ int fft_batched_large(const void *in, void *out, int64_t n, int64_t batch, int d
         return fail(PPX_EINVAL, "large FFT: in and out must not overlap (out holds the intermediate)");
     ppx_fft_plan p;
     if (plan) p = *plan;
-    else if (!fft_tuned_plan(n, p)) fft_default_plan(n, p);
+    else {
+        const DeviceInfo *di = device_info();
+        if (!di) return PPX_EDEVICE;
+        fft_null_plan(n, batch, di->cus, p);
+    }
     int rc = fft_plan_check(n, p);
     if (rc) return rc;
     if (batch * std::max<int64_t>((int64_t(1) << p.log2_n1) / p.tile_a, (n >> p.log2_n1) / p.tile_b) > INT32_MAX)

@@ -154,8 +154,12 @@ std::vector<std::pair<int64_t, ppx_fft_plan>> fft_recorded_plans();  // tuned pl
 void fft_clear_plans();
 void fft_default_plan(int64_t n, ppx_fft_plan &p);
 std::vector<ppx_fft_plan> fft_enumerate_plans(int64_t n);
-bool fft_tuned_plan(int64_t n, ppx_fft_plan &p);
-void fft_record_plan(int64_t n, const ppx_fft_plan &p);
+constexpr int64_t kAnyBatch = INT64_MAX;
+bool fft_tuned_plan(int64_t n, ppx_fft_plan &p, int64_t *batch = nullptr);
+void fft_record_plan(int64_t n, const ppx_fft_plan &p, int64_t batch = kAnyBatch);
+// The plan of a call without one: the recorded or default plan, or, where that
+// leaves CUs without a tile, one of shorter columns and narrower tiles.
+void fft_null_plan(int64_t n, int64_t batch, int cus, ppx_fft_plan &p);
 
 // ---- mixed launch (fused.hip) ----
 struct MixPlan;

@@ -1098,7 +1098,7 @@ static int tune_large_impl(int64_t n, int64_t batch, int method, int max_evals, 
     if (best_us_out) *best_us_out = best_us;
     if (evals_out) *evals_out = method == PPX_TUNE_ANALYTICAL ? 0 : (int)trace.size();
     if (trace_out) *trace_out = trace;
-    fft_record_plan(n, *best_out);
+    fft_record_plan(n, *best_out, batch);
     fail(PPX_OK, "");
     return PPX_OK;
 }
