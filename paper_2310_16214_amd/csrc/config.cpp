@@ -182,10 +182,12 @@ int enumerate_configs(int op, int dtype, int64_t n, ppx_config *out, int cap) {
 //   problems 6.12 and 5.52; n = 2048, 32 problems 4.44 and 4.04; at 2^22
 //   elements radix 16 is the faster one (12.4 against over 12.9).  At n =
 //   4096 the two are equal, below 1024 the tuned radix is 8 already.
-// * Tridiagonal, the CR -> PCR hybrid, WM and LF inside a wave, down to P = 4
-//   while a system still fits one: float32, n = 256, 64 systems 3.29 us at P =
-//   16, 2.67 at P = 4; 1024 systems 4.18 and 3.69; float64, n = 64, 1024
-//   systems 4.15 at P = 8, 3.07 at P = 4.
+// * Tridiagonal, WM and LF inside a wave (their error does not depend on P),
+//   down to P = 4 while a system still fits one: float32, n = 256, 64 systems
+//   4.78 us at P = 16, 2.52 at P = 4; float64, n = 64, 1024 systems 4.62 at P =
+//   8, 3.16 at P = 4.  The CR -> PCR hybrid keeps its P: with fewer equations
+//   per lane more of the work is PCR's, whose error is larger (float32, n =
+//   256: 7.8e-8 at P = 16, 8.3e-8 at 4).
 constexpr int64_t kFullGpuWaves = 1024;  // one per SIMD
 void fit_shape(int op, int dtype, int64_t n, int64_t batch, ppx_config &c) {
     const auto waves = [&] { return n * batch / ((int64_t)c.elems_per_thread * kWave); };
@@ -201,7 +203,7 @@ void fit_shape(int op, int dtype, int64_t n, int64_t batch, ppx_config &c) {
         if (c.radix == 16 && c.elems_per_thread == 16 && (n == 1024 || n == 2048) && waves() <= kFullGpuWaves) halve();
     } else if (op == PPX_OP_TRIDIAG) {
         const int base = tri_base(c.algo);
-        if (base != PPX_TRI_CR_PCR && base != PPX_TRI_WM && base != PPX_TRI_LF) return;
+        if (base != PPX_TRI_WM && base != PPX_TRI_LF) return;
         while (c.elems_per_thread > 4 && n / c.elems_per_thread * 2 <= kWave && waves() < kFullGpuWaves) halve();
     }
 }

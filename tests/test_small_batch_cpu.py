@@ -9,7 +9,7 @@ from paper_2310_16214_amd import ppx
 
 CACHE = os.path.join(os.path.dirname(ppx.__file__), "tuned", "mi355x.txt")
 WAVES = 1024  # a wave per SIMD
-IN_WAVE = (ppx.TRI_CR_PCR, ppx.TRI_WM, ppx.TRI_LF)
+IN_WAVE = (ppx.TRI_WM, ppx.TRI_LF)
 
 
 @pytest.fixture(scope="module", autouse=True)
