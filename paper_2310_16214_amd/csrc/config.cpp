@@ -183,14 +183,20 @@ int enumerate_configs(int op, int dtype, int64_t n, ppx_config *out, int cap) {
 //   elements radix 16 is the faster one (12.4 against over 12.9).  At n =
 //   4096 the two are equal, below 1024 the tuned radix is 8 already.
 // * Tridiagonal, WM and LF inside a wave (their error does not depend on P),
-//   down to P = 4 while a system still fits one: float32, n = 256, 64 systems
-//   4.78 us at P = 16, 2.52 at P = 4; float64, n = 64, 1024 systems 4.62 at P =
-//   8, 3.16 at P = 4.  The CR -> PCR hybrid keeps its P: with fewer equations
+//   down to P = 4 while a system still fits one and there are fewer than four
+//   waves per SIMD: float32, n = 256, 64 systems 4.78 us at P = 16, 2.52 at P =
+//   4, 4096 systems (a wave per SIMD at P = 16) 7.20 and 5.89, 8192 systems
+//   10.00 and 10.12; float64 (two words per value) up to half a wave per SIMD:
+//   n = 64, 1024 systems 4.62 at P = 8, 3.16 at P = 4, 8192 systems 6.42 and
+//   6.76.  The CR -> PCR hybrid keeps its P: with fewer equations
 //   per lane more of the work is PCR's, whose error is larger (float32, n =
 //   256: 7.8e-8 at P = 16, 8.3e-8 at 4).
 constexpr int64_t kFullGpuWaves = 1024;  // one per SIMD
 void fit_shape(int op, int dtype, int64_t n, int64_t batch, ppx_config &c) {
-    const auto waves = [&] { return n * batch / ((int64_t)c.elems_per_thread * kWave); };
+    const auto waves = [&] {
+        const int64_t per = (int64_t)c.elems_per_thread * kWave;
+        return (n * batch + per - 1) / per;
+    };
     const auto halve = [&] {
         c.elems_per_thread /= 2;
         if (op == PPX_OP_FFT) c.radix /= 2;
@@ -204,7 +210,8 @@ void fit_shape(int op, int dtype, int64_t n, int64_t batch, ppx_config &c) {
     } else if (op == PPX_OP_TRIDIAG) {
         const int base = tri_base(c.algo);
         if (base != PPX_TRI_WM && base != PPX_TRI_LF) return;
-        while (c.elems_per_thread > 4 && n / c.elems_per_thread * 2 <= kWave && waves() < kFullGpuWaves) halve();
+        if (waves() * (dtype == PPX_F64 ? 2 : 1) > kFullGpuWaves) return;
+        while (c.elems_per_thread > 4 && n / c.elems_per_thread * 2 <= kWave && waves() < 4 * kFullGpuWaves) halve();
     }
 }
 
