@@ -199,11 +199,12 @@ __device__ __forceinline__ T per_word(T v, F f) {
 }
 
 // Value of lane (lane - 1) across the whole wave (DPP wave_shr:1); lane 0
-// receives 0.  Must be called with all 64 lanes active.
+// receives 0 (by bound_ctrl: with it off, each move needs its destination
+// cleared first).  Must be called with all 64 lanes active.
 constexpr int kDppWaveShr1 = 0x138;
 template <typename T>
 __device__ __forceinline__ T dpp_wave_shr1(T v) {
-    return per_word(v, [](int x) { return __builtin_amdgcn_update_dpp(0, x, kDppWaveShr1, 0xf, 0xf, false); });
+    return per_word(v, [](int x) { return __builtin_amdgcn_update_dpp(0, x, kDppWaveShr1, 0xf, 0xf, true); });
 }
 
 // Value of lane (lane + 1) across the whole wave (DPP wave_shl:1); lane 63
@@ -211,14 +212,14 @@ __device__ __forceinline__ T dpp_wave_shr1(T v) {
 constexpr int kDppWaveShl1 = 0x130;
 template <typename T>
 __device__ __forceinline__ T dpp_wave_shl1(T v) {
-    return per_word(v, [](int x) { return __builtin_amdgcn_update_dpp(0, x, kDppWaveShl1, 0xf, 0xf, false); });
+    return per_word(v, [](int x) { return __builtin_amdgcn_update_dpp(0, x, kDppWaveShl1, 0xf, 0xf, true); });
 }
 
 // Value of lane (lane - D) within the same 16-lane row, 0 where that lane is
 // outside the row.
 template <int D, typename T>
 __device__ __forceinline__ T dpp_row_shr(T v) {
-    return per_word(v, [](int x) { return __builtin_amdgcn_update_dpp(0, x, kDppRowShr + D, 0xf, 0xf, false); });
+    return per_word(v, [](int x) { return __builtin_amdgcn_update_dpp(0, x, kDppRowShr + D, 0xf, 0xf, true); });
 }
 
 // Inclusive scans over aligned segments of seg lanes (a power of two <= 64)

@@ -19,13 +19,15 @@
 //
 // PCR, step with stride s: every equation updates from its neighbours at
 // distance s: for s < P the s nearest equations of the adjacent lanes come by
-// shuffles, from s = P on each equation's neighbours are the same registers of
-// the lanes s/P away.  After log2 n steps x_i = d_i.
+// DPP, from s = P on each equation's neighbours are the same registers of the
+// lanes s/P away.  In the last step (s = n/2) an equation has one neighbour
+// and only needs its d.  After log2 n steps x_i = d_i.
 //
-// Neighbours outside the system are identity rows.  CR replaces them by zeros
-// explicitly.  PCR shuffles within the system's lanes only, so a lane whose
-// neighbour lies outside the system receives one of its own (finite) values,
-// and that value is multiplied by an exact zero: before the step with stride
+// Neighbours outside the system are identity rows.  CR, and PCR's steps with
+// s < P, replace them by zeros explicitly.  PCR's later steps exchange within
+// the system's lanes only, so a lane whose neighbour lies outside the system
+// receives one of its own (finite) values, and that value is multiplied by an
+// exact zero: before the step with stride
 // s, a_i = 0 for every i < s and c_i = 0 for every i >= n - s (true at load,
 // where a_0 = c_{n-1} = 0, and kept by the update, whose new a_i is a product
 // with a_{i-s} and a_i, and new c_i one with c_{i+s} and c_i).  Several
@@ -254,53 +256,80 @@ __device__ __forceinline__ void wave_cr_pcr(T (&a)[P], T (&c)[P], T (&d)[P], int
     cr_inlane_backward<T, P>(a, c, d, dpp_wave_shr1(d[P - 1]), t, P * lps);
 }
 
+// Value of the previous (next) lane of the system by DPP; zeros at the
+// system's ends, where the neighbour row is absent (the lane beyond may belong
+// to another system: its value, even a NaN, is dropped).
+template <typename T>
+__device__ __forceinline__ T lane_before(T v, bool first) {
+    const T x = dpp_wave_shr1(v);
+    return first ? T(0) : x;
+}
+template <typename T>
+__device__ __forceinline__ T lane_after(T v, bool last) {
+    const T x = dpp_wave_shl1(v);
+    return last ? T(0) : x;
+}
+
 // PCR steps with stride S < P, unrolled: the left neighbours of equations
 // r < S are equations P - S + r of the previous lane, the right neighbours of
-// r >= P - S equations r + S - P of the next lane (6 S shuffles per step).
+// r >= P - S equations r + S - P of the next lane (6 S values per step, by
+// DPP: a shuffle would go through the LDS unit, which the steps from P on
+// keep as busy as the vector units).  The equations k, k + S, ... of a
+// residue class only use each other's old values, so each class is updated in
+// place, its old left row carried along, with its six neighbour values
+// fetched first; the scheduling barriers keep the compiler from fetching
+// every class's at once.  With shuffles, every class's neighbours in registers
+// at once and a full last step, PCR was bound by the LDS unit and, at 16
+// equations per lane, by residency (129 VGPRs in f32, now 90; 134 LDS
+// instructions, now 60): n = 1024 f32 24.9 -> 21.1 us at 4096 systems, 48.8 ->
+// 40.2 at 8192; n = 512 f64 93.9 -> 71.5 us at 16384; n = 32 equal (at the
+// memory rate before).
 template <typename T, int P, int S>
-__device__ __forceinline__ void pcr_inlane_steps(T (&a)[P], T (&c)[P], T (&d)[P], int lps) {
+__device__ __forceinline__ void pcr_inlane_steps(T (&a)[P], T (&c)[P], T (&d)[P], bool first, bool last) {
     if constexpr (S < P) {
-        T ua[S], uc[S], ud[S], wa[S], wc[S], wd[S];
 #pragma unroll
         for (int k = 0; k < S; ++k) {
-            ua[k] = sys_up(a[P - S + k], 1, lps);
-            uc[k] = sys_up(c[P - S + k], 1, lps);
-            ud[k] = sys_up(d[P - S + k], 1, lps);
-            wa[k] = sys_down(a[k], 1, lps);
-            wc[k] = sys_down(c[k], 1, lps);
-            wd[k] = sys_down(d[k], 1, lps);
-        }
-        T na[P], nc[P], nd[P];
+            T la = lane_before(a[P - S + k], first);
+            T lc = lane_before(c[P - S + k], first);
+            T ld = lane_before(d[P - S + k], first);
+            const T wa = lane_after(a[k], last);
+            const T wc = lane_after(c[k], last);
+            const T wd = lane_after(d[k], last);
 #pragma unroll
-        for (int r = 0; r < P; ++r) {
-            na[r] = a[r];
-            nc[r] = c[r];
-            nd[r] = d[r];
-            const bool lloc = r >= S, rloc = r + S < P;
-            unit_eliminate(na[r], nc[r], nd[r], lloc ? a[(r + P - S) % P] : ua[r % S],
-                           lloc ? c[(r + P - S) % P] : uc[r % S], lloc ? d[(r + P - S) % P] : ud[r % S],
-                           rloc ? a[(r + S) % P] : wa[(r + S) % S], rloc ? c[(r + S) % P] : wc[(r + S) % S],
-                           rloc ? d[(r + S) % P] : wd[(r + S) % S]);
+            for (int r = k; r < P; r += S) {
+                const T oa = a[r], oc = c[r], od = d[r];
+                const bool local = r + S < P;
+                unit_eliminate(a[r], c[r], d[r], la, lc, ld, local ? a[(r + S) % P] : wa, local ? c[(r + S) % P] : wc,
+                               local ? d[(r + S) % P] : wd);
+                la = oa;
+                lc = oc;
+                ld = od;
+            }
+            if constexpr (P * sizeof(T) >= 32) __builtin_amdgcn_sched_barrier(0);
         }
-#pragma unroll
-        for (int r = 0; r < P; ++r) {
-            a[r] = na[r];
-            c[r] = nc[r];
-            d[r] = nd[r];
-        }
-        pcr_inlane_steps<T, P, 2 * S>(a, c, d, lps);
+        pcr_inlane_steps<T, P, 2 * S>(a, c, d, first, last);
     }
+}
+
+// The last PCR step (stride n/2, lanes dl = lps/2 apart): an equation of the
+// lower half has a right neighbour only, one of the upper half a left one, in
+// the lane with bit dl flipped, and only d is still needed.  k is a lane's
+// remaining coefficient (lower: c, upper: a); kn and dn are the partner's k
+// and d.
+template <typename T>
+__device__ __forceinline__ T pcr_last(T k, T d, T kn, T dn) {
+    return (d - dn * k) * rcp(T(1) - kn * k);
 }
 
 // PCR on the registers of one lane group.
 template <typename T, int P>
-__device__ __forceinline__ void wave_pcr(T (&a)[P], T (&c)[P], T (&d)[P], int lps) {
+__device__ __forceinline__ void wave_pcr(T (&a)[P], T (&c)[P], T (&d)[P], int t, int lps) {
     const int n = P * lps;
-    pcr_inlane_steps<T, P, 1>(a, c, d, lps);
+    pcr_inlane_steps<T, P, 1>(a, c, d, t == 0, t == lps - 1);
     // strides s >= P: the neighbours are the same registers of the lanes s/P
     // away; each equation only needs its own old values and the shuffled
     // ones, so the update is in place (all lanes step through r together)
-    for (int s = P; s < n; s *= 2) {
+    for (int s = P; s < n / 2; s *= 2) {
         const int dl = s / P;
 #pragma unroll
         for (int r = 0; r < P; ++r) {
@@ -311,6 +340,14 @@ __device__ __forceinline__ void wave_pcr(T (&a)[P], T (&c)[P], T (&d)[P], int lp
             // row's shuffles (register pressure would halve the occupancy)
             if constexpr (P * sizeof(T) >= 128)
                 if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    if (lps > 1) {
+        const int dl = lps / 2;
+#pragma unroll
+        for (int r = 0; r < P; ++r) {
+            const T k = t < dl ? c[r] : a[r];
+            d[r] = pcr_last(k, d[r], (T)__shfl_xor(k, dl), (T)__shfl_xor(d[r], dl));
         }
     }
 }
@@ -374,8 +411,8 @@ __device__ __forceinline__ void wave_pcr_reg(T (&a)[P], T (&c)[P], T (&d)[P], in
     constexpr int PL = 64 * K;
     const int n = P * lps;
     const int lane = threadIdx.x & 63;
-    pcr_inlane_steps<T, P, 1>(a, c, d, lps);
-    for (int s = P; s < n; s *= 2) {
+    pcr_inlane_steps<T, P, 1>(a, c, d, t == 0, t == lps - 1);
+    for (int s = P; s < n / 2; s *= 2) {
         const int dl = s / P;
         const int ll = t >= dl ? lane - dl : lane;
         const int rl = t + dl < lps ? lane + dl : lane;
@@ -396,6 +433,23 @@ __device__ __forceinline__ void wave_pcr_reg(T (&a)[P], T (&c)[P], T (&d)[P], in
 #pragma unroll
             for (int k = 0; k < K; ++k)
                 unit_eliminate(a[r0 + k], c[r0 + k], d[r0 + k], la[k], lc[k], ld[k], ra[k], rc[k], rd[k]);
+        }
+    }
+    if (lps > 1) {
+        const int dl = lps / 2;
+#pragma unroll
+        for (int r0 = 0; r0 < P; r0 += K) {
+            T k[K], kn[K], dn[K];
+#pragma unroll
+            for (int j = 0; j < K; ++j) k[j] = t < dl ? c[r0 + j] : a[r0 + j];
+            xstore<T, K>(xb, lane, k);
+            xstore<T, K>(xb + PL, lane, d + r0);
+            wave_lds_order();
+            xload<T, K>(xb, lane ^ dl, kn);
+            xload<T, K>(xb + PL, lane ^ dl, dn);
+            wave_lds_order();
+#pragma unroll
+            for (int j = 0; j < K; ++j) d[r0 + j] = pcr_last(k[j], d[r0 + j], kn[j], dn[j]);
         }
     }
 }
@@ -674,7 +728,7 @@ __device__ __forceinline__ void tridiag_wave_solve(T (&a)[P], const T (&b)[P], T
     }
     if constexpr (ALGO == PPX_TRI_CR_SHFL) wave_cr<T, P>(a, c, d, t, lps);
     else if constexpr (ALGO == PPX_TRI_CR_PCR) wave_cr_pcr<T, P>(a, c, d, t, lps);
-    else if constexpr (ALGO == PPX_TRI_PCR_SHFL) wave_pcr<T, P>(a, c, d, lps);
+    else if constexpr (ALGO == PPX_TRI_PCR_SHFL) wave_pcr<T, P>(a, c, d, t, lps);
     else if constexpr (ALGO == PPX_TRI_WM) wave_wm<T, P>(a, c, d, t, lps);
     else if constexpr (ALGO == PPX_TRI_LF) wave_lf<T, P>(a, c, d, t, lps);
     else wave_pcr_reg<T, P>(a, c, d, t, lps, smem + (tx >> 6) * tri_wave_lds_vals<T, ALGO, P>());
