@@ -31,7 +31,7 @@ __global__ __launch_bounds__(mix_class_block(CLS), CLS == kClassSmall ? 5 : 4) v
     unsigned k = 0;
     while (k + 1 < a.njobs && recs[k + 1].first_tile <= t) ++k;
     const float2 *tw = a.tw;
-    auto body = [&](const MixJob &j, long long first, int count, int tx, int nt) {
+    auto body = [&](const MixJob &j, long long first, int count, int tx, int nt) __attribute__((always_inline)) {
         if constexpr (CLS == kClassSmall) {
             if (j.family == kFamFft256) mix_fft_dispatch<kFamFft256>(j, first, count, tw, lds, tx, nt);
             else if (j.family == kFamScan256) mix_scan_dispatch(j, first, count, wave_tot, tx);
