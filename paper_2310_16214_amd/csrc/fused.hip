@@ -421,23 +421,38 @@ bool mix_args_fit(const char *table, int mask) {
 constexpr int kMixFillPerCu = 4;
 
 // The families of class c whose tiles share the class kernel in a launch:
-// fewest tiles first, as long as together they come to at most three (small)
-// or two (large) workgroups of the class's size per CU.  Families that small
-// leave most of the GPU idle in a kernel of their own, and their kernels'
-// ramps and tails add up: 16 jobs of the serving mix (9.1 M elements) take
-// 40 us against 53 in one kernel per family, 8 jobs with one of every large
-// kind 31.6 against 56.  A family beyond that fills the GPU by itself, at its
-// own occupancy: with no limit, 48 jobs (28-35 M elements) took 155-189 us
-// against 118-156, with the limits 100-136; a limit of ten for the small
-// class costs 16 jobs up to 1.3x, one of one for the large class up to 1.2x.
-static int mix_class_families(int c, int mask, const int64_t *tiles, const int *jobs, int cus) {
-    const int64_t cap = (int64_t)cus * (c == kClassSmall ? 3 : 2);
+// fewest tiles first, as long as together they come to at most 32 (small) or
+// 12 (large) workgroups of the class's size per CU.  Families cut into
+// kernels of their own run one after another, each with its ramp and its
+// tail: 36 launches of 4 to 48 jobs of the serving mix (1-37 M elements) are
+// 1.16 times as fast as with limits of three and two, 1.65 times as fast as
+// with one kernel per family, and no faster without limits.  The limits keep
+// out a family that by itself fills the GPU for long and would run at the
+// class's occupancy (94 registers; in the large class, beside an FFT of n =
+// 16384, one workgroup per CU for its 128 KiB of LDS): beside a small job,
+// scan n = 256 of 2^25 elements takes 58 us shared against 54 apart, of 2^22
+// (16 per CU) 9.5 against 12.5, and two launches of 48 jobs whose small
+// families come to more than 32 per CU lose 4%; beside a few FFTs of n =
+// 16384, scan n = 4096 of 2^23 elements (four per CU) takes 15.8 us shared
+// against 25.0.  The hybrid across waves loses where its own kernel has
+// smaller workgroups (three of 512 threads on a CU hide its barriers, one of
+// 1024 does not): beside a few scans, n = 2048 of 2^22 equations (one per CU)
+// takes 20.4 us shared against 21.1 apart, of 1.5 * 2^22 32.4 against 29.1,
+// of 2^23 39.9 against 35.8; so it then shares up to one tile per CU.  Where a
+// longer system makes its own kernel's workgroups as large as the class's it
+// is as any other (32 jobs with 576 tiles of it and 512 of scan: 72 us
+// shared, 80 apart).
+static int mix_class_families(int c, int mask, const int64_t *tiles, const int *jobs, const unsigned *blocks, int cus) {
+    const int64_t cap = (int64_t)cus * (c == kClassSmall ? 32 : 12);
+    mask &= kMixClassMask[c];
+    for (int f : {kFamTriBlk32, kFamTriBlk32H})
+        if (tiles[f] > cus && (int)blocks[f] < mix_class_block(c)) mask &= ~(1 << f);
     int picked = 0, njobs = 0;
     int64_t total = 0;
     for (;;) {
         int best = -1;
         for (int f = 0; f < kMixFamilies; ++f)
-            if ((mask & kMixClassMask[c] & ~picked & (1 << f)) && (best < 0 || tiles[f] < tiles[best])) best = f;
+            if ((mask & ~picked & (1 << f)) && (best < 0 || tiles[f] < tiles[best])) best = f;
         if (best < 0 || total + tiles[best] > cap || njobs + jobs[best] > kMixClassJobs) break;
         picked |= 1 << best;
         total += tiles[best];
@@ -471,7 +486,7 @@ int mix_enqueue_args(const char *table, int mask, const int *order, int norder, 
             const int64_t threads = (int64_t)h->ntiles[f] * h->block[f];
             tiles[f] = (threads + mix_class_block(c) - 1) / mix_class_block(c);
         }
-        shared[c] = mix_class_families(c, mask, tiles, jobs_of, cus);
+        shared[c] = mix_class_families(c, mask, tiles, jobs_of, h->block, cus);
     }
     // Records of the families in `fams` at workgroup size `block`, appended
     // family by family in the order given, first_tile ascending (as the

@@ -8,10 +8,13 @@
 //          tiles in workgroups of up to 256 threads;
 //   large: T up to 1024 -- FFT (P = 8 and 16), scan and the hybrid across
 //          waves in workgroups of up to 1024 threads.
-// A class kernel runs at its most demanding member's registers (96: five
+// A class kernel runs at its most demanding member's registers (94: five
 // waves per SIMD) and at the LDS of the families present, which is why a
-// family alone, or one whose tiles fill the GPU by themselves, keeps its own
-// kernel (mix_class_families in fused.hip).  The float64 tridiagonal
+// family alone, or one whose tiles fill the GPU for long by themselves, keeps
+// its own kernel (mix_class_families in fused.hip).  The tile body is inlined
+// by attribute: the small class's is past the compiler's limit, and as a
+// function it got the record through scratch memory (a launch of six small
+// scans and one tridiagonal job 8.2 us instead of 4.8).  The float64 tridiagonal
 // families and the LDS solvers need more registers or other LDS and stay
 // apart.  The records come in the kernel arguments, tile b runs in workgroup
 // b, by the same functions as in the family kernels.
