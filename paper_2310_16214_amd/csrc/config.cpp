@@ -177,11 +177,14 @@ int enumerate_configs(int op, int dtype, int64_t n, ppx_config *out, int cap) {
 // SIMD a wave at the tuned values per thread P is bound by the length of one
 // thread's work instead, and takes half the values per thread (the radix with
 // it) as long as that holds:
-// * FFT, radix = P = 16, n = 1024 or 2048: radix 8.  64 problems of n = 1024
-//   in one wave or two each: 3.90 us at radix 16, 3.49 at radix 8; 1024
-//   problems 6.12 and 5.52; n = 2048, 32 problems 4.44 and 4.04; at 2^22
-//   elements radix 16 is the faster one (12.4 against over 12.9).  At n =
-//   4096 the two are equal, below 1024 the tuned radix is 8 already.
+// * FFT, radix = P = 16, n = 256 to 2048: radix 8.  64 problems of n = 1024 in
+//   one wave or two each: 3.90 us at radix 16, 3.49 at radix 8; 1024 problems
+//   6.12 and 5.52; n = 2048, 32 problems 4.44 and 4.04; at 2^22 elements radix
+//   16 is the faster one (12.4 against over 12.9).  At n = 256 and 512 the
+//   lines lie where the two meet: n = 256, 2^20 elements 5.14 us at radix 16,
+//   4.98 at 8, 2^21 7.43 and 7.49, 3 * 2^20 9.65 and 10.0, 2^22 12.1 and 15.9;
+//   n = 512, 2^20 6.04 and 5.06, 3 * 2^20 11.2 and 10.5, 2^22 12.5 and 16.2.
+//   At n = 4096 the two are equal, at 128 and below the tuned radix is 8 or 4.
 // * Tridiagonal, WM and LF inside a wave (their error does not depend on P),
 //   down to P = 4 while a system still fits one and there are fewer than four
 //   waves per SIMD: float32, n = 256, 64 systems 4.78 us at P = 16, 2.52 at P =
@@ -206,7 +209,8 @@ void fit_shape(int op, int dtype, int64_t n, int64_t batch, ppx_config &c) {
         complete_config(op, dtype, n, c);
     };
     if (op == PPX_OP_FFT) {
-        if (c.radix == 16 && c.elems_per_thread == 16 && (n == 1024 || n == 2048) && waves() <= kFullGpuWaves) halve();
+        const int64_t light = n == 256 ? 2 : n == 512 ? 3 : n == 1024 || n == 2048 ? 1 : 0;
+        if (c.radix == 16 && c.elems_per_thread == 16 && waves() <= light * kFullGpuWaves) halve();
     } else if (op == PPX_OP_TRIDIAG) {
         const int base = tri_base(c.algo);
         if (base != PPX_TRI_WM && base != PPX_TRI_LF) return;

@@ -73,3 +73,24 @@ def test_null_call(cuda, tuned, op, dtype, ln):
         else:
             unit = 2.0 ** -24 if dtype == np.float32 else 2.0 ** -53
             assert np.all(np.abs(y - oracle.scan(x)) <= scan_bound(x, unit, oracle_unit=2.0 ** -53))
+
+
+@pytest.mark.parametrize("n,mi", [(256, 2), (512, 3), (1024, 1), (2048, 1)])
+def test_null_fft_around_the_lines(cuda, tuned, n, mi):
+    """Whole calls with one problem less and one more than the mi * 2^20
+    elements where the rule changes the configuration: both sides within the
+    FFT's bound on sampled problems, and nothing stored past the batch."""
+    import torch
+    seen = set()
+    for batch in [(mi << 20) // n - 1, (mi << 20) // n + 1]:
+        seen.add(ppx.resolve_config(ppx.OP_FFT, ppx.C64, n, batch).as_tuple())
+        banner(f"null fft n={n} batch={batch}")
+        g = torch.Generator(device=cuda).manual_seed(n + batch)
+        x = torch.view_as_complex(torch.rand(batch, n, 2, generator=g, device=cuda) * 2 - 1)
+        buf = torch.full((batch * n + 4096,), -7, dtype=x.dtype, device=cuda)
+        ppx.fft_batched(x, buf, n, batch, -1)
+        assert bool((buf[batch * n:] == -7).all()), "stored past the batch"
+        pick = [0, 1, batch // 3, batch // 2, batch - 2, batch - 1]
+        got = to_host(buf[:batch * n].view(batch, n)[pick].contiguous())
+        assert oracle.rel_l2(got, oracle.dft(to_host(x[pick].contiguous()))).max() <= fft_tol(n)
+    assert len(seen) == 2

@@ -10,6 +10,7 @@ from paper_2310_16214_amd import ppx
 CACHE = os.path.join(os.path.dirname(ppx.__file__), "tuned", "mi355x.txt")
 WAVES = 1024  # a wave per SIMD
 IN_WAVE = (ppx.TRI_WM, ppx.TRI_LF)
+LIGHT = {256: 2, 512: 3, 1024: 1, 2048: 1}  # waves per SIMD up to which an FFT takes radix 8
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -35,19 +36,19 @@ def test_fitted_configurations(op, dtype):
             continue  # no entry: the analytical choice, not this rule
         if op == ppx.OP_TRIDIAG and all(ppx.tuned_config(op, dtype, n, a) is None for a in range(8)):
             continue
-        for batch in [1, 2, 3, 5, 7, 64, 100, 255, 1000, 4097, 65536, 1 << 20]:
+        for batch in [1, 2, 3, 5, 7, 64, 100, 255, 1000, 2050, 4097, 8200, 16384, 65536, 1 << 20]:
             c = ppx.resolve_config(op, dtype, n, batch)
             what = (op, dtype, n, batch, c, full)
             assert ppx.config_valid(op, dtype, n, c), what
             assert c.algo == full.algo and c.elems_per_thread * c.threads_per_block == n * c.problems_per_block, what
             if c.as_tuple() == full.as_tuple():
                 continue
-            assert n * batch <= WAVES * full.elems_per_thread * 64, what  # only where it cannot fill the GPU
+            waves = -(-n * batch // (full.elems_per_thread * 64))
             if op == ppx.OP_FFT:
-                assert (full.radix, full.elems_per_thread) == (16, 16) and n in (1024, 2048), what
+                assert (full.radix, full.elems_per_thread) == (16, 16) and waves <= LIGHT[n] * WAVES, what
                 assert (c.radix, c.elems_per_thread) == (8, 8), what
             else:
-                assert op == ppx.OP_TRIDIAG and (full.algo & ~ppx.TRI_PIPE) in IN_WAVE, what
+                assert op == ppx.OP_TRIDIAG and (full.algo & ~ppx.TRI_PIPE) in IN_WAVE and waves <= WAVES, what
                 assert 4 <= c.elems_per_thread < full.elems_per_thread and n // c.elems_per_thread <= 64, what
 
 
