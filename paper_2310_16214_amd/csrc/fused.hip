@@ -363,7 +363,7 @@ int mix_prepare_kernels() {
     for (int c = 0; c < kMixClasses; ++c) {
         int64_t lds = 0;
         for (int f = 0; f < kMixFamilies; ++f)
-            if (kMixClassMask[c] & (1 << f)) lds = std::max(lds, mix_lds_bytes(f));
+            if (kMixClassMask[c] & (1 << f)) lds = std::max<int64_t>(lds, mix_lds_at(f, mix_class_block(c)));
         (void)hipFuncSetAttribute(mix_class_kernel(c), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     }
     g_prepared = true;
@@ -422,9 +422,9 @@ constexpr int kMixFillPerCu = 4;
 
 // The families of class c whose tiles share the class kernel in a launch:
 // fewest tiles first, as long as together they come to at most 32 (small) or
-// 12 (large) workgroups of the class's size per CU.  Families cut into
-// kernels of their own run one after another, each with its ramp and its
-// tail: 36 launches of 4 to 48 jobs of the serving mix (1-37 M elements) are
+// 12 (large) workgroups of the class's size per CU (kClassAll: below).
+// Families cut into kernels of their own run one after another, each with its
+// ramp and its tail: 36 launches of 4 to 48 jobs of the serving mix (1-37 M elements) are
 // 1.16 times as fast as with limits of three and two, 1.65 times as fast as
 // with one kernel per family, and no faster without limits.  The limits keep
 // out a family that by itself fills the GPU for long and would run at the
@@ -442,11 +442,24 @@ constexpr int kMixFillPerCu = 4;
 // longer system makes its own kernel's workgroups as large as the class's it
 // is as any other (32 jobs with 576 tiles of it and 512 of scan: 72 us
 // shared, 80 apart).
+//
+// A launch with families of both classes runs them all in one kernel
+// (kClassAll, 1024-thread workgroups) up to three tiles per CU together: a
+// second kernel's ramp and tail are then a third of the call (8 FFTs of n =
+// 16384 with 4096 systems of 512: 22.0 us in two kernels, 14.5 in one; 64
+// launches of 2 to 16 jobs 1.10 times as fast, none of 20 jobs or more
+// faster).  The small FFTs may be at most a quarter of a tile per CU: one
+// tile of 1024 threads and up to 128 KiB of LDS per CU cannot overlap its
+// loads with its stages as five of 256 threads do (1024 FFTs of n = 1024
+// beside 64 scans of 8192: 9.5 us in one kernel, 10.3 in two; 2048: 12.9 in
+// either; 4096: 19.6 and 16.6).
 static int mix_class_families(int c, int mask, const int64_t *tiles, const int *jobs, const unsigned *blocks, int cus) {
-    const int64_t cap = (int64_t)cus * (c == kClassSmall ? 32 : 12);
-    mask &= kMixClassMask[c];
+    const int64_t cap = (int64_t)cus * (c == kClassSmall ? 32 : c == kClassLarge ? 12 : 3);
+    if (c == kClassAll && (!(mask & kMixClassMask[kClassSmall]) || !(mask & kMixClassMask[kClassLarge]))) return 0;
+    const int all = mask &= kMixClassMask[c];
     for (int f : {kFamTriBlk32, kFamTriBlk32H})
         if (tiles[f] > cus && (int)blocks[f] < mix_class_block(c)) mask &= ~(1 << f);
+    if (c == kClassAll && tiles[kFamFft256] > cus / 4) mask &= ~(1 << kFamFft256);
     int picked = 0, njobs = 0;
     int64_t total = 0;
     for (;;) {
@@ -458,6 +471,7 @@ static int mix_class_families(int c, int mask, const int64_t *tiles, const int *
         total += tiles[best];
         njobs += jobs[best];
     }
+    if (c == kClassAll && picked != all) return 0;
     return __builtin_popcount((unsigned)picked) > 1 ? picked : 0;
 }
 
@@ -480,18 +494,19 @@ int mix_enqueue_args(const char *table, int mask, const int *order, int norder, 
     while (shrink < 1024 && total * shrink * 2 <= fill) shrink *= 2;
     // the families that share each class's kernel
     int shared[kMixClasses];
-    for (int c = 0; c < kMixClasses; ++c) {
+    for (int c = kMixClasses - 1; c >= 0; --c) {  // kClassAll first
         int64_t tiles[kMixFamilies];
         for (int f = 0; f < kMixFamilies; ++f) {
             const int64_t threads = (int64_t)h->ntiles[f] * h->block[f];
             tiles[f] = (threads + mix_class_block(c) - 1) / mix_class_block(c);
         }
-        shared[c] = mix_class_families(c, mask, tiles, jobs_of, h->block, cus);
+        shared[c] = c != kClassAll && shared[kClassAll] ? 0 : mix_class_families(c, mask, tiles, jobs_of, h->block, cus);
     }
-    // Records of the families in `fams` at workgroup size `block`, appended
+    // Records of the families in `fams` at workgroup size `block` (the small
+    // class's with 1/split of the problems a tile could hold), appended
     // family by family in the order given, first_tile ascending (as the
     // kernels scan them).
-    const auto records = [&](int fams, const int *by, int nby, int block, MixJob *out, unsigned *ntiles) {
+    const auto records = [&](int fams, const int *by, int nby, int block, int split, MixJob *out, unsigned *ntiles) {
         unsigned n = 0;
         *ntiles = 0;
         for (int o = 0; o < nby; ++o)
@@ -499,6 +514,7 @@ int mix_enqueue_args(const char *table, int mask, const int *order, int norder, 
                 if (rec[i].family != by[o] || !(fams & (1 << by[o]))) continue;
                 MixJob r = rec[i];
                 r.per_tile = (int)((int64_t)r.per_tile * block / (int)h->block[by[o]]);
+                if (kMixClassMask[kClassSmall] & (1 << by[o])) r.per_tile = std::max(1, r.per_tile / split);
                 r.first_tile = *ntiles;
                 *ntiles += (unsigned)((r.batch + r.per_tile - 1) / r.per_tile);
                 out[n++] = r;
@@ -530,12 +546,30 @@ int mix_enqueue_args(const char *table, int mask, const int *order, int norder, 
             const int block = shrink > 1 ? std::max(full / shrink, widest(fams)) : full;
             // the families with the longest tiles first, so that none of
             // those is the last to start
-            static constexpr int by[kMixClasses][5] = {
-                {kFamTriW32H, kFamFft256, kFamTriW32, kFamScan256, -1},
-                {kFamFft1024, kFamTriBlk32H, kFamFft1024P8, kFamTriBlk32, kFamScan1024}};
+            static constexpr int by[kMixClasses][9] = {
+                {kFamTriW32H, kFamFft256, kFamTriW32, kFamScan256},
+                {kFamFft1024, kFamTriBlk32H, kFamFft1024P8, kFamTriBlk32, kFamScan1024},
+                {kFamFft1024, kFamTriBlk32H, kFamFft1024P8, kFamTriBlk32, kFamTriW32H, kFamFft256, kFamTriW32, kFamScan1024,
+                 kFamScan256}};
+            static constexpr int nby[kMixClasses] = {4, 5, 9};
             MixClassArgs a;
             a.tw = tw;
-            a.njobs = records(fams, by[c], c == kClassSmall ? 4 : 5, block, a.jobs, &a.ntiles);
+            // kClassAll's workgroups are as wide as its widest problem: where
+            // that leaves CUs without a tile, the small families' tiles take
+            // fewer problems (and leave the rest of their threads idle), down
+            // to a wave's worth (64 scans of n = 8192 with 4096 systems of 64:
+            // 9.0 us without, 6.4 with, 7.5 in two kernels)
+            int split = 1;
+            if (c == kClassAll) {
+                int64_t small = 0, large = 0;
+                for (int q = 0; q < kMixFamilies; ++q) {
+                    if (!(fams & (1 << q))) continue;
+                    const int64_t t = ((int64_t)h->ntiles[q] * h->block[q] + block - 1) / block;
+                    (kMixClassMask[kClassSmall] & (1 << q) ? small : large) += t;
+                }
+                while (split < block / kWave && large + small * split * 2 <= cus) split *= 2;
+            }
+            a.njobs = records(fams, by[c], nby[c], block, split, a.jobs, &a.ntiles);
             size_t lds = 0;
             for (int q = 0; q < kMixFamilies; ++q)
                 if (fams & (1 << q)) lds = std::max(lds, mix_lds_at(q, block));
@@ -546,7 +580,7 @@ int mix_enqueue_args(const char *table, int mask, const int *order, int norder, 
             const int block = shrink > 1 && f != kFamTriLds ? std::max(full / shrink, widest(fams)) : full;
             MixArgs a;
             a.tables = nullptr;
-            a.njobs = records(fams, &f, 1, block, a.jobs, &a.ntiles);
+            a.njobs = records(fams, &f, 1, block, 1, a.jobs, &a.ntiles);
             hipLaunchKernelGGL(reinterpret_cast<mix_kernel_t>(const_cast<void *>(mix_kernel(f, true))),
                                dim3(a.ntiles), dim3(block), mix_lds_at(f, block), s, a, tw);
         }

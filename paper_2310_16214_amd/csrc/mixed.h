@@ -140,10 +140,12 @@ static_assert(sizeof(MixArgs) <= 4096 - 64, "kernel arguments are limited to 4 K
 // Classes of families that share a kernel in an argument launch
 // (mixed_class.hip), their workgroup sizes, and what their kernels are
 // launched with.
-enum MixClass : int { kClassSmall = 0, kClassLarge, kMixClasses };
+enum MixClass : int { kClassSmall = 0, kClassLarge, kClassAll, kMixClasses };
 constexpr int kMixClassMask[kMixClasses] = {
     1 << kFamFft256 | 1 << kFamScan256 | 1 << kFamTriW32 | 1 << kFamTriW32H,
-    1 << kFamFft1024 | 1 << kFamFft1024P8 | 1 << kFamScan1024 | 1 << kFamTriBlk32 | 1 << kFamTriBlk32H};
+    1 << kFamFft1024 | 1 << kFamFft1024P8 | 1 << kFamScan1024 | 1 << kFamTriBlk32 | 1 << kFamTriBlk32H,
+    1 << kFamFft256 | 1 << kFamScan256 | 1 << kFamTriW32 | 1 << kFamTriW32H | 1 << kFamFft1024 | 1 << kFamFft1024P8 |
+        1 << kFamScan1024 | 1 << kFamTriBlk32 | 1 << kFamTriBlk32H};
 constexpr int mix_class_block(int cls) { return cls == kClassSmall ? 256 : 1024; }
 constexpr int kMixClassJobs = 54;
 struct MixClassArgs {

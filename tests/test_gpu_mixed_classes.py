@@ -22,6 +22,13 @@ LAUNCHES = {
     # 30 + 30 records of two families of one class: more than its kernel takes
     "records": [(S, 64, 3 + k) for k in range(30)] + [(F, 128, 2 + k) for k in range(30)] + [(T, 32, 5), (T, 64, 5)],
     # one family with far more tiles than the limit, next to small ones
+    # small families over more than one of the larger workgroups' tiles, ragged
+    "all": [(F, 16, 300), (F, 64, 70), (F, 512, 19), (F, 4096, 5), (S, 16, 1030), (S, 256, 33), (T, 16, 1027), (T, 64, 67),
+            (T, 512, 19)] + LARGE,
+    # small FFTs past their share of the kernel of both classes
+    "all-limit": [(F, 1024, 1100), (T, 64, 67)] + LARGE,
+    # a small family past the limit of its own class
+    "small-limit": SMALL + [(S, 64, 140001)],
     "limit": SMALL + [(S, 64, 60001), (F, 16384, 600), (T, 8192, 1), (S, 16384, 1)],
 }
 
