@@ -113,13 +113,25 @@ __device__ __forceinline__ void wave_store(T *dst, const T (&v)[P]) {
 // fetched together, and the last equation then goes through its levels
 // (cr_inlane_last): the same eliminations, with one exchange between lanes
 // instead of one per level.
+//
+// The left half of the last equation's first elimination needs nothing from
+// the next lane and is done with the others, before any exchange: its right
+// side d = D * (1 / b) from the load is then only ever a term of a
+// multiply-add, unrounded.  (A barrier between the two would round it, and
+// with it every right side of the reduced system.)
+template <typename T>
+struct CrLast {
+    T den, num, a;  // 1 - lc a, d - ld a, -(la a)
+};
 template <typename T, int P>
-__device__ __forceinline__ void cr_inlane_local(T (&a)[P], T (&c)[P], T (&d)[P]) {
+__device__ __forceinline__ CrLast<T> cr_inlane_local(T (&a)[P], T (&c)[P], T (&d)[P]) {
+    const CrLast<T> last{T(1) - c[P - 2] * a[P - 1], d[P - 1] - d[P - 2] * a[P - 1], -(a[P - 2] * a[P - 1])};
 #pragma unroll
     for (int s = 1; 2 * s < P; s *= 2)
 #pragma unroll
         for (int r = 2 * s - 1; r < P - 1; r += 2 * s)
             unit_eliminate(a[r], c[r], d[r], a[r - s], c[r - s], d[r - s], a[r + s], c[r + s], d[r + s]);
+    return last;
 }
 
 // na[k], nc[k], nd[k]: equation 2^k - 1 of the next lane (zeros past the
@@ -127,10 +139,15 @@ __device__ __forceinline__ void cr_inlane_local(T (&a)[P], T (&c)[P], T (&d)[P])
 template <int P>
 constexpr int cr_levels() { return P == 2 ? 1 : P == 4 ? 2 : P == 8 ? 3 : 4; }
 template <typename T, int P>
-__device__ __forceinline__ void cr_inlane_last(T (&a)[P], T (&c)[P], T (&d)[P], const T (&na)[cr_levels<P>()],
-                                               const T (&nc)[cr_levels<P>()], const T (&nd)[cr_levels<P>()], int n) {
+__device__ __forceinline__ void cr_inlane_last(T (&a)[P], T (&c)[P], T (&d)[P], const CrLast<T> &last,
+                                               const T (&na)[cr_levels<P>()], const T (&nc)[cr_levels<P>()],
+                                               const T (&nd)[cr_levels<P>()], int n) {
+    const T r = rcp(last.den - na[0] * c[P - 1]);
+    d[P - 1] = (last.num - nd[0] * c[P - 1]) * r;
+    a[P - 1] = last.a * r;
+    c[P - 1] = -(nc[0] * c[P - 1]) * r;
 #pragma unroll
-    for (int k = 0; k < cr_levels<P>(); ++k) {
+    for (int k = 1; k < cr_levels<P>(); ++k) {
         const int s = 1 << k;
         if (2 * s <= n / 2)  // the last level leaves two equations
             unit_eliminate(a[P - 1], c[P - 1], d[P - 1], a[P - 1 - s], c[P - 1 - s], d[P - 1 - s], na[k], nc[k], nd[k]);
@@ -139,7 +156,7 @@ __device__ __forceinline__ void cr_inlane_last(T (&a)[P], T (&c)[P], T (&d)[P], 
 
 template <typename T, int P>
 __device__ __forceinline__ void cr_inlane_forward(T (&a)[P], T (&c)[P], T (&d)[P], int t, int lps) {
-    cr_inlane_local<T, P>(a, c, d);
+    const CrLast<T> cl = cr_inlane_local<T, P>(a, c, d);
     const bool last_lane = t + 1 == lps;
     constexpr int K = cr_levels<P>();
     T na[K], nc[K], nd[K];
@@ -151,7 +168,7 @@ __device__ __forceinline__ void cr_inlane_forward(T (&a)[P], T (&c)[P], T (&d)[P
         nd[k] = dpp_wave_shl1(d[e]);
         if (last_lane) na[k] = nc[k] = nd[k] = T(0);
     }
-    cr_inlane_last<T, P>(a, c, d, na, nc, nd, P * lps);
+    cr_inlane_last<T, P>(a, c, d, cl, na, nc, nd, P * lps);
 }
 
 // CR back substitution inside the lane (s < P), once every lane's last
@@ -848,6 +865,11 @@ __device__ __forceinline__ TriRow<T> row_eliminate(TriRow<T> r, const TriRow<T> 
 template <typename T, int P>
 __device__ __forceinline__ void block_cr_pcr(T (&a)[P], T (&c)[P], T (&d)[P], int t, int lps, int tx, int L,
                                              T *xs, T *last) {
+    // n for the in-lane levels, all of which run (lps > 64): a constant, so no
+    // branch ends the blocks in which products and sums become multiply-adds
+    // (n = 4096, float32, error against 64 bits: 7.90e-8 with such branches,
+    // 7.82e-8 without; float64 1.68e-16 and 1.63e-16)
+    constexpr int kManyLanes = 1 << 30;
     int set = 0;
     auto slots = [&]() {
         T *w = xs + (set & 1) * 3 * L;
@@ -855,7 +877,7 @@ __device__ __forceinline__ void block_cr_pcr(T (&a)[P], T (&c)[P], T (&d)[P], in
         return w;
     };
     // ---- CR forward levels inside the lane
-    cr_inlane_local<T, P>(a, c, d);
+    const CrLast<T> cl = cr_inlane_local<T, P>(a, c, d);
     {
         constexpr int K = cr_levels<P>();
         T na[K], nc[K], nd[K];
@@ -889,7 +911,7 @@ __device__ __forceinline__ void block_cr_pcr(T (&a)[P], T (&c)[P], T (&d)[P], in
                 nd[k] = w[((wave + 1) * K + k) * 3 + 2];
             }
         }
-        cr_inlane_last<T, P>(a, c, d, na, nc, nd, P * lps);
+        cr_inlane_last<T, P>(a, c, d, cl, na, nc, nd, kManyLanes);
     }
     // ---- PCR on the lanes' last equations
     TriRow<T> r{a[P - 1], c[P - 1], d[P - 1]};
@@ -925,7 +947,7 @@ __device__ __forceinline__ void block_cr_pcr(T (&a)[P], T (&c)[P], T (&d)[P], in
     // ---- the previous lane's last unknown, then back substitution in the lane
     last[tx] = r.d;
     __syncthreads();
-    cr_inlane_backward<T, P>(a, c, d, t > 0 ? last[tx - 1] : T(0), t, P * lps);
+    cr_inlane_backward<T, P>(a, c, d, t > 0 ? last[tx - 1] : T(0), t, kManyLanes);
 }
 
 // LDS values of a workgroup of L threads: the two slot sets, or, where the
