@@ -4,7 +4,8 @@
 //
 // A launch with at most kMixArgJobs jobs in every family passes each
 // family's job records in the kernel arguments: one kernel launch per
-// family, a workgroup per tile, nothing else.  Any other launch copies one
+// family, or per class of families that share one (mixed_class.hip), a
+// workgroup per tile, nothing else.  Any other launch copies one
 // table (header and job records) from pinned memory to the device and
 // enqueues [expand the tile lists] -> [family kernel] -> ..., each family
 // kernel persistent (at most as many workgroups as are resident, and no more
