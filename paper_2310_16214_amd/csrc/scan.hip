@@ -88,8 +88,14 @@ static void launch_t(const void *k, dim3 g, dim3 b, hipStream_t s, const void *i
                        static_cast<const T *>(in), static_cast<T *>(out), log2n, (long long)batch, gb);
 }
 
-int launch_scan(const void *in, void *out, int log2n, int64_t batch, int dtype, const ppx_config &c,
+int launch_scan(const void *in, void *out, int log2n, int64_t batch, int dtype, const ppx_config &cfg,
                 hipStream_t s, bool exclusive) {
+    // The kernels' rows are 64 vectors: a thread's vectors lie a whole wave's
+    // apart.  A configuration of fewer threads runs as a wave of the same
+    // problems (P and with it each problem's arithmetic unchanged, more of
+    // them per workgroup).
+    ppx_config c = cfg;
+    for (; c.threads_per_block < kWave; c.threads_per_block *= 2) c.problems_per_block *= 2;
     const void *k = scan_kernel(dtype, c.elems_per_thread, c.algo, exclusive);
     if (!k) return fail(PPX_ECONFIG, "no scan kernel for this dtype / elements-per-thread / algo");
     int64_t grid = (batch + c.problems_per_block - 1) / c.problems_per_block;

@@ -1,8 +1,9 @@
 // Batched inclusive and exclusive sum scans (Sec. III "Scan Operator" of
 // arXiv:2310.16214), int32 (modulo 2^32), float32 and float64, for gfx950.
 //
-// A workgroup of L threads scans G_b problems of size n, i.e. G_b*n contiguous
-// elements, P per thread: each wave takes 64*P consecutive elements, as R =
+// A workgroup of L threads (whole waves: launch_scan sees to it) scans G_b
+// problems of size n, i.e. G_b*n contiguous elements, P per thread: each wave
+// takes 64*P consecutive elements, as R =
 // P / V rows of 64 vectors (V elements, 16 bytes; fewer where P is), and lane
 // l holds vector l of each row.  So every load and store instruction moves
 // 1 KiB of consecutive bytes.  (With a thread's P elements consecutive
