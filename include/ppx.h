@@ -20,10 +20,18 @@
  *   Compute calls are asynchronous and stream-ordered.
  * - `cfg` may be NULL: the library then uses the configuration recorded by
  *   tune() for (op, dtype, n) if there is one, else the analytical model's
- *   choice.  A batch too small to fill the GPU with a recorded configuration
- *   takes fewer values per thread (ppx_resolve_config says which), and fewer
- *   problems per workgroup, which changes no result.  An explicit cfg is validated (ppx_config_valid) and rejected
- *   with PPX_ECONFIG if it does not describe a valid launch.
+ *   choice.  A batch of the recorded one (the batch tune() was given) or more
+ *   takes that configuration as it is, and so does every batch where the
+ *   entry came from a file that does not say its batch.  A smaller batch may
+ *   take fewer values per thread (ppx_resolve_config says which: for an FFT
+ *   another radix, for a tridiagonal solver another split of a system over
+ *   its lanes, so its results may differ in the last bits from those of the
+ *   same problem in a larger batch), and fewer problems per workgroup, which
+ *   changes no result.  A persistent configuration (the _PIPE algorithms)
+ *   whose batch leaves every workgroup one group runs its plain twin: the same
+ *   bits for scans and tridiagonal solves, for FFTs the last bits may differ.
+ *   An explicit cfg is validated (ppx_config_valid) and rejected with
+ *   PPX_ECONFIG if it does not describe a valid launch.
  * - Every call returns PPX_OK (0) or a negative PPX_E* code; a message is
  *   then available from ppx_last_error() (thread-local).  Argument checks run
  *   before any HIP runtime call, so they need no GPU.
@@ -187,7 +195,9 @@ typedef struct ppx_fft_plan {
  * holds the intermediate between the passes).  plan == NULL: the plan
  * tune_fft_large recorded for n, else ppx_default_fft_plan; a batch with
  * fewer tiles than CUs in one of that plan's passes, and smaller than the one
- * it was tuned at, takes a plan of shorter columns and narrower tiles.  Errors:
+ * it was tuned at (a plan from a file that does not say its batch is kept for
+ * every call), takes a plan of shorter columns and narrower tiles, whose
+ * results may differ in the last bits.  Errors:
  * PPX_EINVAL (pointers, n, batch, direction, overlap), PPX_ECONFIG (plan).
  * fft_batched with such an n and cfg == NULL forwards here.
  */
@@ -220,7 +230,7 @@ int ppx_default_fft_plan(int64_t n, ppx_fft_plan *out);
  * and both tile widths), ANALYTICAL applies the occupancy guideline to each
  * pass's kernels separately over its (radix, tile) choices and takes the
  * most even split.
- * The winner is recorded for fft_batched_large(plan == NULL).
+ * The winner is recorded, with its batch, for fft_batched_large(plan == NULL).
  */
 int tune_fft_large(int64_t n, int64_t batch, int method, int max_evals, ppx_fft_plan *best,
                    double *best_us, int *evals_used);
@@ -265,8 +275,10 @@ int tridiag_batched(const void *a, const void *b, const void *c, const void *d,
 /*
  * tune -- Sec. IV (analytical and learned tuning) and Sec. VI (exhaustive
  * search as the reference).  Chooses a configuration for (op, dtype, n) at
- * the given batch on the current device and records it in the tune cache,
- * where later calls with cfg == NULL find it.
+ * the given batch on the current device and records it with that batch in the
+ * tune cache, where later calls with cfg == NULL find it: calls of that batch
+ * or a larger one launch exactly this configuration, smaller ones may fit it
+ * to their batch (see the conventions above).
  *   method     PPX_TUNE_EXHAUSTIVE | PPX_TUNE_ANALYTICAL | PPX_TUNE_LEARNED
  *   max_evals  cap on timed candidates (<= 0: no cap); ignored for
  *              ANALYTICAL, which times nothing.
@@ -422,8 +434,10 @@ int ppx_default_config(int op, int dtype, int64_t n, ppx_config *out);
 
 /*
  * ppx_resolve_config -- what a call with cfg == NULL will use for
- * (op, dtype, n): the tuned entry if one is cached, else the analytical
- * choice.  Needs no GPU when the analytical choice comes from the static
+ * (op, dtype, n, batch): the tuned entry if one is cached (for a batch smaller
+ * than the one it was tuned at, with the values per thread fitted to the
+ * batch), else the analytical choice; a batch with few workgroups then runs
+ * them with fewer problems each, which changes no result.  Needs no GPU when the analytical choice comes from the static
  * resource table.
  */
 int ppx_resolve_config(int op, int dtype, int64_t n, int64_t batch,

@@ -237,9 +237,9 @@ int ppx_stream_reference(const void *const *in, int k, void *out, int64_t bytes,
  * Tune cache: tuned configurations keyed by (op, dtype, n, algo filter) for
  * the running device architecture, and tuned large-FFT plans keyed by n.
  * Text file, one entry per line:
- *   arch op dtype n algo radix P L G_b S algo_cfg us method
- *   arch plan n log2_n1 radix_a radix_b tile_a tile_b us method
- * load merges the file into memory (returns the number of entries taken;
+ *   arch op dtype n algo radix P L G_b S algo_cfg us method [batch]
+ *   arch plan n log2_n1 radix_a radix_b tile_a tile_b us method [batch]
+ * batch: the one the entry was tuned at (absent or 0: not known).  load merges the file into memory (returns the number of entries taken;
  * entries no longer valid are skipped); save writes every entry; clear
  * empties both kinds.
  */

@@ -133,15 +133,20 @@ static int check_shape(int64_t n, int64_t batch, int64_t elem_bytes) {
     return PPX_OK;
 }
 
-static int resolve(int op, int dtype, int64_t n, int64_t batch, const ppx_config *cfg,
-                   ppx_config &c) {
+// as_is: the configuration is the caller's, or was recorded by a tuning at
+// this batch or a smaller one, and is launched as it stands; another recorded
+// or analytical one may be fitted to the batch (fit_shape, fit_groups).
+static int resolve(int op, int dtype, int64_t n, int64_t batch, const ppx_config *cfg, ppx_config &c, bool &as_is) {
+    as_is = cfg != nullptr;
     if (cfg) {
         c = *cfg;
         complete_config(op, dtype, n, c);
         return validate_config(op, dtype, n, c);
     }
-    if (cached_config(op, dtype, n, c)) {
-        fit_shape(op, dtype, n, batch, c);
+    int64_t tuned_batch;
+    if (cached_config(op, dtype, n, c, tuned_batch)) {
+        as_is = batch >= tuned_batch;
+        if (!as_is) fit_shape(op, dtype, n, batch, c);
         return PPX_OK;
     }
     return analytical_config(op, dtype, n, batch, c);
@@ -156,8 +161,8 @@ static int resolve(int op, int dtype, int64_t n, int64_t batch, const ppx_config
 // float32 tridiagonal, n = 1024, 16 systems 4.10 -> 3.49, 256 systems 4.72 ->
 // 4.5; n = 256 FFT, 4096 problems 5.56 -> 5.25.  With four workgroups per CU
 // or more the resolved shape stays (it is tuned for full grids).
-static void fit_groups(int op, int dtype, int64_t n, int64_t batch, const ppx_config *cfg, ppx_config &c) {
-    const DeviceInfo *di = cfg ? nullptr : device_info_if_ready();
+static void fit_groups(int op, int dtype, int64_t n, int64_t batch, bool as_is, ppx_config &c) {
+    const DeviceInfo *di = as_is ? nullptr : device_info_if_ready();
     if (!di) return;
     while (c.problems_per_block > 1 && c.threads_per_block > kMinThreadsPerBlock &&
            (batch + c.problems_per_block - 1) / c.problems_per_block < 4 * (int64_t)di->cus) {
@@ -190,8 +195,9 @@ int fft_batched(const void *in, void *out, int64_t n, int64_t batch, int directi
     if (rc) return rc;
     if (overlap_partial(in, out, batch * n * 8)) return fail(PPX_EINVAL, "in and out overlap partially");
     ppx_config c;
-    if ((rc = resolve(PPX_OP_FFT, PPX_C64, n, batch, cfg, c))) return rc;
-    fit_groups(PPX_OP_FFT, PPX_C64, n, batch, cfg, c);
+    bool as_is;
+    if ((rc = resolve(PPX_OP_FFT, PPX_C64, n, batch, cfg, c, as_is))) return rc;
+    fit_groups(PPX_OP_FFT, PPX_C64, n, batch, as_is, c);
     if ((batch + c.problems_per_block - 1) / c.problems_per_block > INT32_MAX)
         return fail(PPX_EINVAL, "too many workgroups");
     return launch_fft(in, out, ilog2(n), batch, c, direction == 1, static_cast<hipStream_t>(stream));
@@ -262,8 +268,9 @@ static int scan_common(const void *in, void *out, int64_t n, int64_t batch, int 
     if (rc) return rc;
     if (overlap_partial(in, out, batch * n * es)) return fail(PPX_EINVAL, "in and out overlap partially");
     ppx_config c;
-    if ((rc = resolve(PPX_OP_SCAN, dtype, n, batch, cfg, c))) return rc;
-    fit_groups(PPX_OP_SCAN, dtype, n, batch, cfg, c);
+    bool as_is;
+    if ((rc = resolve(PPX_OP_SCAN, dtype, n, batch, cfg, c, as_is))) return rc;
+    fit_groups(PPX_OP_SCAN, dtype, n, batch, as_is, c);
     if ((batch + c.problems_per_block - 1) / c.problems_per_block > INT32_MAX)
         return fail(PPX_EINVAL, "too many workgroups");
     if (!device_info()) return PPX_EDEVICE;
@@ -298,8 +305,9 @@ int tridiag_batched(const void *a, const void *b, const void *c, const void *d, 
             return fail(PPX_EINVAL, "x may alias d only");
     if (overlap_partial(d, x, bytes)) return fail(PPX_EINVAL, "x and d overlap partially");
     ppx_config cc;
-    if ((rc = resolve(PPX_OP_TRIDIAG, dtype, n, batch, cfg, cc))) return rc;
-    fit_groups(PPX_OP_TRIDIAG, dtype, n, batch, cfg, cc);
+    bool as_is;
+    if ((rc = resolve(PPX_OP_TRIDIAG, dtype, n, batch, cfg, cc, as_is))) return rc;
+    fit_groups(PPX_OP_TRIDIAG, dtype, n, batch, as_is, cc);
     if ((batch + cc.problems_per_block - 1) / cc.problems_per_block > INT32_MAX)
         return fail(PPX_EINVAL, "too many workgroups");
     return launch_tridiag(a, b, c, d, x, ilog2(n), batch, dtype, cc, static_cast<hipStream_t>(stream));
@@ -323,7 +331,8 @@ int ppx_resolve_config(int op, int dtype, int64_t n, int64_t batch, ppx_config *
     t_err.clear();
     if (!out) return fail(PPX_EINVAL, "null output");
     if (batch < 1) return fail(PPX_EINVAL, "batch must be >= 1");
-    return resolve(op, dtype, n, batch, nullptr, *out);
+    bool as_is;
+    return resolve(op, dtype, n, batch, nullptr, *out, as_is);
 }
 
 int ppx_enumerate_configs(int op, int dtype, int64_t n, ppx_config *out, int cap) {

@@ -640,19 +640,14 @@ void fft_default_plan(int64_t n, ppx_fft_plan &p) {
 
 namespace {
 std::mutex g_plan_mu;
-struct RecordedPlan {
-    ppx_fft_plan plan;
-    int64_t batch;  // the batch it was tuned at (kAnyBatch: read from a file, which does not say)
-};
 std::map<int64_t, RecordedPlan> g_plans;  // tuned plans by n
 }  // namespace
 
-bool fft_tuned_plan(int64_t n, ppx_fft_plan &p, int64_t *batch) {
+bool fft_tuned_plan(int64_t n, RecordedPlan &r) {
     std::lock_guard<std::mutex> lk(g_plan_mu);
     auto it = g_plans.find(n);
     if (it == g_plans.end()) return false;
-    p = it->second.plan;
-    if (batch) *batch = it->second.batch;
+    r = it->second;
     return true;
 }
 
@@ -661,11 +656,9 @@ void fft_record_plan(int64_t n, const ppx_fft_plan &p, int64_t batch) {
     g_plans[n] = RecordedPlan{p, batch};
 }
 
-std::vector<std::pair<int64_t, ppx_fft_plan>> fft_recorded_plans() {
+std::vector<std::pair<int64_t, RecordedPlan>> fft_recorded_plans() {
     std::lock_guard<std::mutex> lk(g_plan_mu);
-    std::vector<std::pair<int64_t, ppx_fft_plan>> out;
-    for (const auto &e : g_plans) out.emplace_back(e.first, e.second.plan);
-    return out;
+    return std::vector<std::pair<int64_t, RecordedPlan>>(g_plans.begin(), g_plans.end());
 }
 
 // The plan of a call that gives none.  A recorded (or the default) plan is for
@@ -678,13 +671,18 @@ std::vector<std::pair<int64_t, ppx_fft_plan>> fft_recorded_plans() {
 // 2^16 17.1 -> 10.8, 2^17 20.4 -> 12.8, 2^18 20.9 -> 13.4, 2^20 27.1 -> 19.0,
 // 2^21 35.1 -> 28.7; at 2^22 elements per call (a tile for every CU in both
 // passes) the recorded plans win again or are even (2^20 x 4 41.8 against
-// 42.2, 2^21 x 2 43.0 both).  A plan tuned in this process at the call's batch
-// or a smaller one is kept as it is.
+// 42.2, 2^21 x 2 43.0 both).  A plan tuned at the call's batch or a smaller
+// one is kept as it is.
 void fft_null_plan(int64_t n, int64_t batch, int cus, ppx_fft_plan &p) {
-    int64_t tuned_batch = kAnyBatch;
-    if (!fft_tuned_plan(n, p, &tuned_batch)) fft_default_plan(n, p);
+    RecordedPlan r;
+    if (fft_tuned_plan(n, r)) {
+        p = r.plan;
+        if (batch >= r.batch) return;
+    } else {
+        fft_default_plan(n, p);
+    }
     const int64_t tiles_a = (int64_t(1) << p.log2_n1) / p.tile_a, tiles_b = (n >> p.log2_n1) / p.tile_b;
-    if (batch >= tuned_batch || batch * std::min(tiles_a, tiles_b) >= cus) return;
+    if (batch * std::min(tiles_a, tiles_b) >= cus) return;
     const int ln = ilog2(n), l1 = ln <= 18 ? ln - 9 : (ln - 1) / 2, l2 = ln - l1;
     ppx_fft_plan q{l1, l2 <= 9 ? 8 : 16, l1 <= 10 ? 8 : 16, 0, 0};
     const auto width = [&](int radix, int log2len, int log2cols, bool pass_a) {

@@ -150,13 +150,19 @@ int64_t fft_tile_lds_bytes(int radix, int log2len, int tile, bool pass_a);
 int launch_fft_large(const void *in, void *out, int log2n, int64_t batch, const ppx_fft_plan &p, bool inverse,
                      hipStream_t s);
 int fft_plan_check(int64_t n, const ppx_fft_plan &p);  // PPX_OK or a failure with reason
-std::vector<std::pair<int64_t, ppx_fft_plan>> fft_recorded_plans();  // tuned plans by n
 void fft_clear_plans();
 void fft_default_plan(int64_t n, ppx_fft_plan &p);
 std::vector<ppx_fft_plan> fft_enumerate_plans(int64_t n);
-constexpr int64_t kAnyBatch = INT64_MAX;
-bool fft_tuned_plan(int64_t n, ppx_fft_plan &p, int64_t *batch = nullptr);
-void fft_record_plan(int64_t n, const ppx_fft_plan &p, int64_t batch = kAnyBatch);
+// A tuned plan and the batch it was tuned at; calls of that batch or a larger
+// one use it as it is.  kUnknownBatch (a file that does not say): every call.
+constexpr int64_t kUnknownBatch = 0;
+struct RecordedPlan {
+    ppx_fft_plan plan;
+    int64_t batch;
+};
+bool fft_tuned_plan(int64_t n, RecordedPlan &r);
+void fft_record_plan(int64_t n, const ppx_fft_plan &p, int64_t batch);
+std::vector<std::pair<int64_t, RecordedPlan>> fft_recorded_plans();  // by n
 // The plan of a call without one: the recorded or default plan, or, where that
 // leaves CUs without a tile, one of shorter columns and narrower tiles.
 void fft_null_plan(int64_t n, int64_t batch, int cus, ppx_fft_plan &p);
@@ -194,8 +200,9 @@ int analytical_config(int op, int dtype, int64_t n, int64_t batch, ppx_config &c
 // The configuration of a tridiagonal call restricted to one family (tuned
 // entry of the family, else the analytical choice within it).
 int family_config(int dtype, int64_t n, int64_t batch, int family, ppx_config &c);
-// tune cache (tune.cpp): entry recorded for (op, dtype, n, any algorithm)
-bool cached_config(int op, int dtype, int64_t n, ppx_config &c);
+// tune cache (tune.cpp): entry recorded for (op, dtype, n, any algorithm) and
+// the batch it was tuned at (kUnknownBatch where a file does not say)
+bool cached_config(int op, int dtype, int64_t n, ppx_config &c, int64_t &batch);
 void store_cached_config(int op, int dtype, int64_t n, const ppx_config &c);
 
 }  // namespace ppx

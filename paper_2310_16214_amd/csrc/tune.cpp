@@ -507,37 +507,36 @@ struct CacheEntry {
     ppx_config cfg;
     double us;
     int method;
+    int64_t batch;  // it was tuned at (kUnknownBatch where a file does not say)
 };
 std::map<std::tuple<int, int, int64_t, int>, CacheEntry> g_cache;  // (op, dtype, n, algo filter)
 }  // namespace
 
 // The entry for (op, dtype, n) over every algorithm; if only per-algorithm
 // (per-family) entries were tuned, the fastest of them.
-bool cached_config(int op, int dtype, int64_t n, ppx_config &c) {
+bool cached_config(int op, int dtype, int64_t n, ppx_config &c, int64_t &batch) {
     std::lock_guard<std::mutex> lk(g_cache_mu);
     auto it = g_cache.find({op, dtype, n, -1});
-    if (it != g_cache.end()) {
-        c = it->second.cfg;
-        return true;
-    }
-    const CacheEntry *best = nullptr;
-    for (int a = 0; a <= kTriMaxBase; ++a) {
+    const CacheEntry *best = it != g_cache.end() ? &it->second : nullptr;
+    const bool any = best != nullptr;
+    for (int a = 0; !any && a <= kTriMaxBase; ++a) {
         auto jt = g_cache.find({op, dtype, n, a});
         if (jt != g_cache.end() && jt->second.us > 0 && (!best || jt->second.us < best->us)) best = &jt->second;
     }
     if (!best) return false;
     c = best->cfg;
+    batch = best->batch;
     return true;
 }
 
-static void cache_put(int op, int dtype, int64_t n, int algo, const ppx_config &c, double us,
-                      int method) {
+static void cache_put(int op, int dtype, int64_t n, int algo, const ppx_config &c, double us, int method,
+                      int64_t batch) {
     std::lock_guard<std::mutex> lk(g_cache_mu);
-    g_cache[{op, dtype, n, algo}] = CacheEntry{c, us, method};
+    g_cache[{op, dtype, n, algo}] = CacheEntry{c, us, method, batch};
 }
 
 void store_cached_config(int op, int dtype, int64_t n, const ppx_config &c) {
-    cache_put(op, dtype, n, -1, c, 0.0, -1);
+    cache_put(op, dtype, n, -1, c, 0.0, -1, kUnknownBatch);
 }
 
 // ============================================================ resources
@@ -980,7 +979,7 @@ static int tune_impl(int op, int dtype, int64_t n, int64_t batch, int method, in
             rep->trace_cfg[i] = trace[i].first;
             rep->trace_us[i] = trace[i].second;
         }
-    cache_put(op, dtype, n, algo, cands[best], best_us, method);
+    cache_put(op, dtype, n, algo, cands[best], best_us, method, batch);
     fail(PPX_OK, "");
     return PPX_OK;
 }
@@ -1229,6 +1228,12 @@ int ppx_kernel_resources(int op, int dtype, int64_t n, const ppx_config *cfg, pp
     return resources(op, dtype, n, c, true, *out);
 }
 
+// The batch that may end a tune cache line (kUnknownBatch where it does not).
+static int64_t read_batch(std::istream &is) {
+    int64_t batch;
+    return is >> batch && batch > 0 ? batch : kUnknownBatch;
+}
+
 int ppx_tune_cache_load(const char *path) {
     if (!path) return fail(PPX_EINVAL, "null path");
     std::ifstream f(path);
@@ -1249,7 +1254,7 @@ int ppx_tune_cache_load(const char *path) {
                   method))
                 return fail(PPX_EINVAL, "malformed tune cache line: " + line);
             if (fft_plan_check(n, p) != PPX_OK) continue;  // stale entry
-            fft_record_plan(n, p);
+            fft_record_plan(n, p, read_batch(is));
             ++count;
             continue;
         }
@@ -1264,7 +1269,7 @@ int ppx_tune_cache_load(const char *path) {
         ppx_config v = c;
         complete_config(op, dtype, n, v);
         if (validate_config(op, dtype, n, v) != PPX_OK) continue;  // stale entry
-        cache_put(op, dtype, n, algo, v, us, method);
+        cache_put(op, dtype, n, algo, v, us, method, read_batch(is));
         ++count;
     }
     fail(PPX_OK, "");
@@ -1275,20 +1280,21 @@ int ppx_tune_cache_save(const char *path) {
     if (!path) return fail(PPX_EINVAL, "null path");
     std::ofstream f(path);
     if (!f) return fail(PPX_EINVAL, std::string("cannot write ") + path);
-    f << "# arch op dtype n algo_filter radix P L G_b S algo us method\n";
+    f << "# arch op dtype n algo_filter radix P L G_b S algo us method batch\n";
     std::lock_guard<std::mutex> lk(g_cache_mu);
     for (const auto &kv : g_cache) {
         const auto &c = kv.second.cfg;
         f << "gfx950 " << std::get<0>(kv.first) << ' ' << std::get<1>(kv.first) << ' '
           << std::get<2>(kv.first) << ' ' << std::get<3>(kv.first) << ' ' << c.radix << ' '
           << c.elems_per_thread << ' ' << c.threads_per_block << ' ' << c.problems_per_block << ' '
-          << c.lds_elems << ' ' << c.algo << ' ' << kv.second.us << ' ' << kv.second.method << '\n';
+          << c.lds_elems << ' ' << c.algo << ' ' << kv.second.us << ' ' << kv.second.method << ' '
+          << kv.second.batch << '\n';
     }
-    f << "# arch plan n log2_n1 radix_a radix_b tile_a tile_b us method (tuned large-FFT plans)\n";
+    f << "# arch plan n log2_n1 radix_a radix_b tile_a tile_b us method batch (tuned large-FFT plans)\n";
     for (const auto &np : fft_recorded_plans()) {
-        const ppx_fft_plan &p = np.second;
+        const ppx_fft_plan &p = np.second.plan;
         f << "gfx950 plan " << np.first << ' ' << p.log2_n1 << ' ' << p.radix_a << ' ' << p.radix_b << ' '
-          << p.tile_a << ' ' << p.tile_b << " 0 -1\n";
+          << p.tile_a << ' ' << p.tile_b << " 0 -1 " << np.second.batch << '\n';
     }
     return f ? PPX_OK : fail(PPX_EINVAL, "write failed");
 }
@@ -1304,7 +1310,9 @@ int ppx_tune_cache_clear(void) {
 
 int ppx_tuned_fft_plan(int64_t n, ppx_fft_plan *out) {
     if (!out) return fail(PPX_EINVAL, "null output");
-    if (!fft_tuned_plan(n, *out)) return fail(PPX_EINVAL, "no tuned plan for this n");
+    RecordedPlan r;
+    if (!fft_tuned_plan(n, r)) return fail(PPX_EINVAL, "no tuned plan for this n");
+    *out = r.plan;
     return PPX_OK;
 }
 
