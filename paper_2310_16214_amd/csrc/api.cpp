@@ -218,16 +218,18 @@ int fft_batched_large(const void *in, void *out, int64_t n, int64_t batch, int d
     if (pi < po + bytes && po < pi + bytes)
         return fail(PPX_EINVAL, "large FFT: in and out must not overlap (out holds the intermediate)");
     ppx_fft_plan p;
+    bool as_is = true;
     if (plan) p = *plan;
-    else {
-        const DeviceInfo *di = device_info();
-        if (!di) return PPX_EDEVICE;
-        fft_null_plan(n, batch, di->cus, p);
-    }
+    else as_is = fft_null_plan(n, batch, p);
     int rc = fft_plan_check(n, p);
     if (rc) return rc;
     if (batch * std::max<int64_t>((int64_t(1) << p.log2_n1) / p.tile_a, (n >> p.log2_n1) / p.tile_b) > INT32_MAX)
         return fail(PPX_EINVAL, "too many workgroups");
+    if (!as_is) {
+        const DeviceInfo *di = device_info();
+        if (!di) return PPX_EDEVICE;
+        fft_fill_plan(n, batch, di->cus, p);
+    }
     return launch_fft_large(in, out, ilog2(n), batch, p, direction == 1, static_cast<hipStream_t>(stream));
 }
 

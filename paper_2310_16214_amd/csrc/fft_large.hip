@@ -661,26 +661,26 @@ std::vector<std::pair<int64_t, RecordedPlan>> fft_recorded_plans() {
     return std::vector<std::pair<int64_t, RecordedPlan>>(g_plans.begin(), g_plans.end());
 }
 
-// The plan of a call that gives none.  A recorded (or the default) plan is for
-// a full GPU: long columns in wide tiles, each tile most of a CU's LDS.  Where
-// one of its passes has fewer tiles than CUs, the call is bound by the length
-// of one tile's work, and takes short columns instead (as even a split as
+bool fft_null_plan(int64_t n, int64_t batch, ppx_fft_plan &p) {
+    RecordedPlan r;
+    const bool recorded = fft_tuned_plan(n, r);
+    if (recorded) p = r.plan;
+    else fft_default_plan(n, p);
+    return recorded && batch >= r.batch;
+}
+
+// A recorded (or the default) plan is for a full GPU: long columns in wide
+// tiles, each tile most of a CU's LDS.  Where one of its passes has fewer tiles
+// than CUs, the call is bound by the length of one tile's work, and takes short
+// columns instead (as even a split as
 // radix 8 allows: n2 = 512 up to n = 2^18, then n1 = 2^((log2 n - 1) / 2)), in
 // the widest tiles that still give every CU one, down to four columns and 256
 // threads.  One problem, recorded plan against this: 2^15 12.4 -> 10.0 us,
 // 2^16 17.1 -> 10.8, 2^17 20.4 -> 12.8, 2^18 20.9 -> 13.4, 2^20 27.1 -> 19.0,
 // 2^21 35.1 -> 28.7; at 2^22 elements per call (a tile for every CU in both
 // passes) the recorded plans win again or are even (2^20 x 4 41.8 against
-// 42.2, 2^21 x 2 43.0 both).  A plan tuned at the call's batch or a smaller
-// one is kept as it is.
-void fft_null_plan(int64_t n, int64_t batch, int cus, ppx_fft_plan &p) {
-    RecordedPlan r;
-    if (fft_tuned_plan(n, r)) {
-        p = r.plan;
-        if (batch >= r.batch) return;
-    } else {
-        fft_default_plan(n, p);
-    }
+// 42.2, 2^21 x 2 43.0 both).
+void fft_fill_plan(int64_t n, int64_t batch, int cus, ppx_fft_plan &p) {
     const int64_t tiles_a = (int64_t(1) << p.log2_n1) / p.tile_a, tiles_b = (n >> p.log2_n1) / p.tile_b;
     if (batch * std::min(tiles_a, tiles_b) >= cus) return;
     const int ln = ilog2(n), l1 = ln <= 18 ? ln - 9 : (ln - 1) / 2, l2 = ln - l1;

@@ -163,9 +163,12 @@ struct RecordedPlan {
 bool fft_tuned_plan(int64_t n, RecordedPlan &r);
 void fft_record_plan(int64_t n, const ppx_fft_plan &p, int64_t batch);
 std::vector<std::pair<int64_t, RecordedPlan>> fft_recorded_plans();  // by n
-// The plan of a call without one: the recorded or default plan, or, where that
-// leaves CUs without a tile, one of shorter columns and narrower tiles.
-void fft_null_plan(int64_t n, int64_t batch, int cus, ppx_fft_plan &p);
+// The plan of a call without one: the recorded plan or the default one.
+// True if it is for calls of this batch as it is.
+bool fft_null_plan(int64_t n, int64_t batch, ppx_fft_plan &p);
+// Where plan p leaves CUs without a tile: a plan of shorter columns and
+// narrower tiles instead.
+void fft_fill_plan(int64_t n, int64_t batch, int cus, ppx_fft_plan &p);
 
 // ---- mixed launch (fused.hip) ----
 struct MixPlan;
