@@ -146,7 +146,10 @@ static int resolve(int op, int dtype, int64_t n, int64_t batch, const ppx_config
     int64_t tuned_batch;
     if (cached_config(op, dtype, n, c, tuned_batch)) {
         as_is = batch >= tuned_batch;
-        if (!as_is) fit_shape(op, dtype, n, batch, c);
+        if (!as_is) {
+            const DeviceInfo *di = device_info_if_ready();
+            fit_shape(op, dtype, n, batch, di ? di->cus : kDefaultCus, c);
+        }
         return PPX_OK;
     }
     return analytical_config(op, dtype, n, batch, c);

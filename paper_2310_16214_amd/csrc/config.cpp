@@ -173,29 +173,31 @@ int enumerate_configs(int op, int dtype, int64_t n, ppx_config *out, int cap) {
     return count;
 }
 
-// A tuned shape is the fastest on a full GPU.  A call too small to give every
-// SIMD a wave at the tuned values per thread P is bound by the length of one
-// thread's work instead, and takes half the values per thread (the radix with
-// it) as long as that holds:
-// * FFT, radix = P = 16, n = 256 to 2048: radix 8.  64 problems of n = 1024 in
-//   one wave or two each: 3.90 us at radix 16, 3.49 at radix 8; 1024 problems
-//   6.12 and 5.52; n = 2048, 32 problems 4.44 and 4.04; at 2^22 elements radix
-//   16 is the faster one (12.4 against over 12.9).  At n = 256 and 512 the
-//   lines lie where the two meet: n = 256, 2^20 elements 5.14 us at radix 16,
-//   4.98 at 8, 2^21 7.43 and 7.49, 3 * 2^20 9.65 and 10.0, 2^22 12.1 and 15.9;
-//   n = 512, 2^20 6.04 and 5.06, 3 * 2^20 11.2 and 10.5, 2^22 12.5 and 16.2.
-//   At n = 4096 the two are equal, at 128 and below the tuned radix is 8 or 4.
-// * Tridiagonal, WM and LF inside a wave (their error does not depend on P),
-//   down to P = 4 while a system still fits one and there are fewer than four
-//   waves per SIMD: float32, n = 256, 64 systems 4.78 us at P = 16, 2.52 at P =
-//   4, 4096 systems (a wave per SIMD at P = 16) 7.20 and 5.89, 8192 systems
-//   10.00 and 10.12; float64 (two words per value) up to half a wave per SIMD:
-//   n = 64, 1024 systems 4.62 at P = 8, 3.16 at P = 4, 8192 systems 6.42 and
-//   6.76.  The CR -> PCR hybrid keeps its P: with fewer equations
-//   per lane more of the work is PCR's, whose error is larger (float32, n =
-//   256: 7.8e-8 at P = 16, 8.3e-8 at 4).
-constexpr int64_t kFullGpuWaves = 1024;  // one per SIMD
-void fit_shape(int op, int dtype, int64_t n, int64_t batch, ppx_config &c) {
+// A tuned shape is the fastest on a full GPU.  A smaller call is bound by the
+// length of one thread's work instead, and takes fewer values per thread (P;
+// of an FFT the radix with it).  How few waves that takes differs: each line
+// below is where the two shapes meet, in waves per SIMD at the tuned P (the
+// device's CUs have four SIMDs each), measured with 256 CUs:
+// * FFT, radix = P = 16: radix 8 up to one wave per SIMD at n = 1024 and 2048,
+//   two at n = 256, three at n = 512.  64 problems of n = 1024 in one wave or
+//   two each: 3.90 us at radix 16, 3.49 at radix 8; 1024 problems 6.12 and
+//   5.52; n = 2048, 32 problems 4.44 and 4.04; at 2^22 elements radix 16 is
+//   the faster one (12.4 against over 12.9).  n = 256, 2^20 elements (a
+//   wave per SIMD) 5.14 us at radix 16, 4.98 at 8, 2^21 7.43 and 7.49, 3 * 2^20
+//   9.65 and 10.0, 2^22 12.1 and 15.9; n = 512, 2^20 6.04 and 5.06, 3 * 2^20
+//   11.2 and 10.5, 2^22 12.5 and 16.2.  At n = 4096 the two are equal, at 128
+//   and below the tuned radix is 8 or 4.
+// * Tridiagonal, WM and LF inside a wave (their error does not depend on P), in
+//   calls of up to one wave per SIMD (float64: half a wave): P halves, down to
+//   4, while a system still fits a wave and there are fewer than four waves per
+//   SIMD at the P reached.  float32, n = 256, 64 systems 4.78 us at P = 16,
+//   2.52 at P = 4, 4096 systems (a wave per SIMD at P = 16) 7.20 and 5.89, 8192
+//   systems 10.00 and 10.12; float64, n = 64, 1024 systems 4.62 at P = 8, 3.16
+//   at P = 4, 8192 systems 6.42 and 6.76.  The CR -> PCR hybrid keeps its P:
+//   with fewer equations per lane more of the work is PCR's, whose error is
+//   larger (float32, n = 256: 7.8e-8 at P = 16, 8.3e-8 at 4).
+void fit_shape(int op, int dtype, int64_t n, int64_t batch, int cus, ppx_config &c) {
+    const int64_t simds = 4 * (int64_t)cus;
     const auto waves = [&] {
         const int64_t per = (int64_t)c.elems_per_thread * kWave;
         return (n * batch + per - 1) / per;
@@ -210,12 +212,12 @@ void fit_shape(int op, int dtype, int64_t n, int64_t batch, ppx_config &c) {
     };
     if (op == PPX_OP_FFT) {
         const int64_t light = n == 256 ? 2 : n == 512 ? 3 : n == 1024 || n == 2048 ? 1 : 0;
-        if (c.radix == 16 && c.elems_per_thread == 16 && waves() <= light * kFullGpuWaves) halve();
+        if (c.radix == 16 && c.elems_per_thread == 16 && waves() <= light * simds) halve();
     } else if (op == PPX_OP_TRIDIAG) {
         const int base = tri_base(c.algo);
         if (base != PPX_TRI_WM && base != PPX_TRI_LF) return;
-        if (waves() * (dtype == PPX_F64 ? 2 : 1) > kFullGpuWaves) return;
-        while (c.elems_per_thread > 4 && n / c.elems_per_thread * 2 <= kWave && waves() < 4 * kFullGpuWaves) halve();
+        if (waves() * (dtype == PPX_F64 ? 2 : 1) > simds) return;
+        while (c.elems_per_thread > 4 && n / c.elems_per_thread * 2 <= kWave && waves() < 4 * simds) halve();
     }
 }
 

@@ -28,6 +28,7 @@ constexpr int kMaxElemsPerThread = 32;
 // registers of a 1024-thread workgroup).
 constexpr int kScanF64MaxElems = 16;
 constexpr int64_t kStaticLdsPerBlock = 160 * 1024;  // gfx950 LDS per CU
+constexpr int kDefaultCus = 256;  // of an MI355X, where no device is ready to ask
 
 struct DeviceInfo {
     int device = -1;
@@ -196,8 +197,8 @@ int validate_config(int op, int dtype, int64_t n, const ppx_config &c);
 void complete_config(int op, int dtype, int64_t n, ppx_config &c);
 int default_config(int op, int dtype, int64_t n, ppx_config &c);
 // The values per thread of a tuned configuration for a batch too small to
-// fill the GPU with it (rule in config.cpp).
-void fit_shape(int op, int dtype, int64_t n, int64_t batch, ppx_config &c);
+// fill a GPU of `cus` CUs with it (rule in config.cpp).
+void fit_shape(int op, int dtype, int64_t n, int64_t batch, int cus, ppx_config &c);
 int enumerate_configs(int op, int dtype, int64_t n, ppx_config *out, int cap);
 int analytical_config(int op, int dtype, int64_t n, int64_t batch, ppx_config &c);
 // The configuration of a tridiagonal call restricted to one family (tuned
