@@ -542,15 +542,35 @@ void store_cached_config(int op, int dtype, int64_t n, const ppx_config &c) {
 // ============================================================ resources
 // VGPR counts reported by the compiler for these kernels, used only
 // when no device is present to ask (CPU-side resolution of a NULL config).
-static int static_vgprs(int op, int dtype, int P, int algo) {
+// By log2(P) - 1; the in-wave tridiagonal kernels by variant first
+// (PPX_TRI_CR_PCR to PPX_TRI_LF), then plain and persistent.
+static int static_vgprs(int op, int dtype, int64_t n, int P, int algo) {
     if (op == PPX_OP_FFT) return P <= 2 ? 16 : P <= 4 ? 29 : P <= 8 ? 55 : P <= 16 ? 107 : 200;
-    if (op == PPX_OP_SCAN)
-        return (dtype == PPX_F64 ? 2 : 1) * (P <= 2 ? 10 : P <= 4 ? 12 : P <= 8 ? 16 : P <= 16 ? 24 : 40);
-    if (tri_in_wave(algo))
-        return (dtype == PPX_F64 ? 2 : 1) *
-                   (tri_base(algo) == PPX_TRI_PCR_SHFL || tri_base(algo) == PPX_TRI_PCR_REG ? 6 : 5) * P *
-                   ((algo & PPX_TRI_PIPE) ? 2 : 1) + 16;
-    return dtype == PPX_F64 ? (algo == PPX_TRI_PCR ? 44 : 40) : (algo == PPX_TRI_PCR ? 32 : 28);
+    const bool f64 = dtype == PPX_F64;
+    const int lp = std::max(0, ilog2(P) - 1);
+    if (op == PPX_OP_SCAN) {
+        static constexpr int plain[2][5] = {{9, 11, 16, 30, 58}, {16, 20, 36, 68}};
+        static constexpr int pipe[2][2][5] = {{{16, 20, 34, 52, 91}, {22, 26, 38, 59, 103}},
+                                              {{20, 32, 60, 108}, {26, 36, 64, 112}}};
+        return (algo & PPX_SCAN_KS_PIPE) ? pipe[f64][algo & PPX_SCAN_LF][lp] : plain[f64][lp];
+    }
+    if (tri_blk(algo, n, P)) {
+        static constexpr int blk[2][4] = {{31, 37, 50, 78}, {58, 70, 92, 151}};
+        return blk[f64][std::min(lp, 3)];
+    }
+    if (tri_in_wave(algo)) {
+        static constexpr int wave[2][2][6][4] = {
+            {{{19, 35, 59, 93}, {22, 28, 46, 86}, {25, 43, 57, 81},
+              {26, 48, 65, 90}, {17, 28, 39, 78}, {24, 30, 42, 73}},
+             {{24, 50, 115, 229}, {30, 45, 94, 184}, {24, 40, 75, 155},
+              {34, 62, 90, 148}, {26, 39, 73, 165}, {37, 51, 80, 138}}},
+            {{{34, 66, 100, 148}, {36, 48, 88, 140}, {44, 59, 102, 160},
+              {46, 68, 104, 157}, {34, 46, 82, 152}, {48, 60, 84, 136}},
+             {{35, 123, 245, 364}, {52, 82, 152, 318}, {44, 75, 149, 296},
+              {62, 114, 220, 320}, {49, 77, 135, 263}, {69, 97, 157, 284}}}};
+        return wave[f64][(algo & PPX_TRI_PIPE) != 0][tri_base(algo) - PPX_TRI_CR_PCR][std::min(lp, 3)];
+    }
+    return f64 ? (algo == PPX_TRI_PCR ? 34 : 33) : (algo == PPX_TRI_PCR ? 24 : 21);
 }
 
 static const void *kernel_for(int op, int dtype, int64_t n, const ppx_config &c) {
@@ -579,7 +599,7 @@ static int resources(int op, int dtype, int64_t n, const ppx_config &c, bool hav
                      ppx_resource &r) {
     r.threads = c.threads_per_block;
     r.lds_bytes = (int32_t)dyn_lds(op, dtype, n, c);
-    r.regs_per_thread = static_vgprs(op, dtype, c.elems_per_thread, c.algo);
+    r.regs_per_thread = static_vgprs(op, dtype, n, c.elems_per_thread, c.algo);
     if (have_device) {
         const void *k = kernel_for(op, dtype, n, c);
         hipFuncAttributes a;
