@@ -128,10 +128,15 @@ extern "C" {
  *                       log2(r) the first FFT stage uses the lower radix
  *                       2^(log2 n mod log2 r).
  *   elems_per_thread    P = n * G_b / L; 0 means "derive from L and G_b".
- *   threads_per_block   L in {64,128,256,512,1024}.
+ *   threads_per_block   L, a power of two up to 1024 (the tuners search
+ *                       64 to 1024; a scan of fewer than 64 runs as 64 threads
+ *                       with more problems per workgroup).
  *   problems_per_block  G_b in {1,2,4,...}; G_b * n = P * L.
  *   lds_elems           S, elements held in LDS per workgroup; 0 on input
  *                       means "derive"; ppx_resolve_config reports the value.
+ *                       For the hybrid across waves its exchange slots only
+ *                       (two per thread), whose buffer also stages the
+ *                       solution: ppx_kernel_resources gives the bytes.
  *   algo                PPX_FFT_*, PPX_SCAN_* or PPX_TRI_*.
  */
 typedef struct ppx_config {
@@ -330,13 +335,16 @@ typedef struct ppx_job {
  * Each job is cut into tiles of the shape its single call uses with
  * cfg == NULL (the tuned configuration, else the analytical one;
  * tridiagonal: of the job's family): the same radix, values per thread and
- * solver, so each job's output equals that single call's and does not
- * depend on what else shares the launch.  The tiles run in one kernel per
- * family of tile shapes (FFT, scan and tridiagonal by block size and
- * register demand).  A launch with at most PPX_MIXED_ARG_JOBS jobs in every
- * family passes the job records in the kernel arguments, one workgroup per
- * tile: one kernel launch per family and nothing else.  A larger launch
- * copies its tables to the device (one of 4 ring slots), expands the tile
+ * solver, so each job's output equals that single call's (but for the last
+ * bits of an FFT whose single call runs a persistent kernel: the compiler
+ * contracts its products and sums in other places) and does not depend on
+ * what else shares the launch.  The tiles run by families of tile
+ * shapes (FFT, scan and tridiagonal by block size and register demand).  A
+ * launch with at most PPX_MIXED_ARG_JOBS jobs in every family passes the job
+ * records in the kernel arguments, one workgroup per tile, and consists of
+ * kernel launches alone: one per family, or one for several families whose
+ * tiles together are few (the float32 families of one workgroup size, or of
+ * both sizes in the smallest launches).  A larger launch copies its tables to the device (one of 4 ring slots), expands the tile
  * lists and runs persistent kernels that claim tiles from per-family
  * counters.  Asynchronous and stream-ordered; allocates nothing after a
  * device's first mixed launch, which creates the ring slots.  At most 16384
@@ -363,8 +371,8 @@ int launch_mixed(const ppx_job *jobs, int njobs, void *stream);
  * caller passes the inputs and outputs.  The first call on a device sets it
  * up (device state, occupancy queries, the array's address) without
  * allocating; later calls only plan on the host and enqueue, on `stream`,
- * what launch_mixed does: the argument kernels for a launch with few jobs
- * per family (the array unused), else a few table copy kernels, the
+ * what launch_mixed does: the argument kernels, of one family or of several,
+ * for a launch with few jobs per family (the array unused), else a few table copy kernels, the
  * tile-list expansion and the persistent family kernels.
  * Every call on a device shares that device's array, so calls whose work
  * overlaps on one device (different streams, or host threads) race and must
@@ -388,7 +396,7 @@ int launch_mixed_noalloc(const ppx_job *jobs, int njobs, void *stream);
  * (if not NULL) the single-call configuration whose arithmetic the tiles
  * follow:
  * the configuration of the job's call with cfg == NULL, with the persistent
- * flag cleared (a launch strategy, not arithmetic); for a job that runs as
+ * flag cleared (a launch strategy); for a job that runs as
  * its own call (PPX_MIXED_DIRECT_ELEMS), that configuration unchanged and its
  * problems per workgroup; for an FFT whose tuned
  * shape is not radix = P in {8, 16} (or 4 with n <= 1024), the radix = P

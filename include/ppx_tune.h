@@ -79,9 +79,8 @@ int ppx_device_model_gfx950(ppx_device_model *out);
  *       of steps 1-2 from 60% to 50% of W^max (four waves per SIMD).
  * Writes the chosen index to *chosen.  The library's own analytical choice
  * (tune() with PPX_TUNE_ANALYTICAL, and a NULL config with nothing tuned)
- * uses GRID_FILL | WINDOW_50 over the candidates whose global accesses are
- * coalesced per instruction (for the scan: P <= 4, one 16-byte vector per
- * lane).
+ * uses GRID_FILL | WINDOW_50, for the scan over the candidates of one 16-byte
+ * vector per lane (P <= 4; where there is none, of the smallest P).
  */
 #define PPX_ANALYTICAL_GRID_FILL 1
 #define PPX_ANALYTICAL_WINDOW_50 4

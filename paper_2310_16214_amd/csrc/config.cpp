@@ -40,7 +40,9 @@ static int lds_elems(int op, int64_t n, const ppx_config &c) {
             return T > kWave ? c.threads_per_block / kWave : 0;
         }
         default:
-            if (tri_blk(c.algo, n, c.elems_per_thread)) return 2 * c.threads_per_block;  // lane slots, two sets
+            // the exchange slots, two per thread (tri_blk_lds_vals has the
+            // allocation, which also stages the solution)
+            if (tri_blk(c.algo, n, c.elems_per_thread)) return 2 * c.threads_per_block;
             if (tri_in_wave(c.algo)) return 0;
             return (int)((c.algo == PPX_TRI_PCR ? 2 : 1) * c.problems_per_block * n);
     }

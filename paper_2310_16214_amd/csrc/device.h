@@ -106,8 +106,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t group_rsrc(const void *base, l
 // of which is the input staying cached between the calls.  The hint needs
 // stores that cover whole lines (a lane storing a contiguous chunk of 64
 // bytes, one quarter per instruction, is slower with it): the scan and
-// tridiagonal kernels use it where theirs do.  Loads keep the default policy: on a plain copy, hinting
-// both directions was slower than hinting the stores alone.
+// tridiagonal kernels use it where theirs do.  Loads keep the default policy:
+// on a plain copy, hinting both directions was slower than hinting the stores
+// alone.
 constexpr int kStoreNT = 2;
 
 __device__ __forceinline__ void store_nt(unsigned *p, unsigned v) { __builtin_nontemporal_store(v, p); }

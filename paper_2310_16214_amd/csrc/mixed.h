@@ -126,7 +126,7 @@ int64_t mix_lds_bytes(int fam);
 // has at most kMixArgJobs jobs passes each family's job records here
 // (first_tile counted within the family) to the family's argument kernel,
 // whose workgroup b runs tile b: no table in device memory, no expansion, no
-// counter, one launch per family.  Any other launch passes the device tables
+// counter, one launch per family or per class of families (below).  Any other launch passes the device tables
 // (tables) to the persistent kernels, which claim tiles from the counters.
 constexpr int kMixArgJobs = PPX_MIXED_ARG_JOBS;
 struct MixArgs {

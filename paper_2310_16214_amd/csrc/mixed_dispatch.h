@@ -99,8 +99,8 @@ __device__ __forceinline__ void mix_triw_dispatch(const MixJob &j, long long fir
 }
 
 // The hybrid across waves: a tile is nt / (n / P) systems (nt the workgroup
-// size), the lanes exchanging through LDS slots (two sets of a, c, d per
-// thread).
+// size), the lanes exchanging through LDS slots, which also stage the solution
+// where a lane holds 64 bytes or more of it (tri_blk_lds_vals).
 template <int FAM, int LP>
 __device__ __forceinline__ void mix_trib_dispatch(const MixJob &j, long long first, int count, void *smem, int tx,
                                                   int nt) {

@@ -610,14 +610,14 @@ static int resources(int op, int dtype, int64_t n, const ppx_config &c, bool hav
     return PPX_OK;
 }
 
-// Premise (i) of the analytical model (coalesced global accesses) restated
-// for these kernels on gfx950: the scan kernel gives each lane P contiguous
-// elements, so a load instruction is contiguous across the wave only when
-// those P elements are one 16-byte vector (P * element size <= 16); where no
-// such configuration exists (large n) the smallest P comes closest.  The FFT
-// and tridiagonal kernels read consecutive elements with consecutive lanes
-// for every P.
-static bool coalesced(int op, int dtype, const ppx_config &c) {
+// Scan shapes the analytical model ranks: one 16-byte vector per lane (P *
+// element size <= 16), and where no such configuration exists (large n) the
+// smallest P.  This was premise (i), coalesced global accesses, for kernels
+// that gave each lane P contiguous elements; the kernels' rows of vectors are
+// contiguous for every P now, and the rule stands on measurement: the tuned
+// scans up to n = 2048 are all of one vector per lane (above, P is 4 to 16).
+// The FFT and tridiagonal shapes are not restricted.
+static bool one_vector(int op, int dtype, const ppx_config &c) {
     return op != PPX_OP_SCAN || c.elems_per_thread * elem_bytes(op, dtype) <= 16;
 }
 
@@ -637,7 +637,7 @@ static int persistent_flag(int op) {
 constexpr int kGfx950Flags = PPX_ANALYTICAL_GRID_FILL | PPX_ANALYTICAL_WINDOW_50;
 
 // The candidates the gfx950 guideline ranks:
-//  * coalesced ones (above);
+//  * scans: one vector per lane (above);
 //  * no persistent variants: the occupancy model does not see what they
 //    change; the choice is mapped to its persistent twin afterwards (see
 //    analytical_select);
@@ -654,8 +654,8 @@ static std::vector<ppx_config> analytical_candidates(int op, int dtype, const st
     if (base.empty()) base = all;
     std::vector<ppx_config> out;
     for (const auto &c : base)
-        if (coalesced(op, dtype, c)) out.push_back(c);
-    if (out.empty()) {  // no fully coalesced shape: the smallest P
+        if (one_vector(op, dtype, c)) out.push_back(c);
+    if (out.empty()) {  // none: the smallest P
         int pmin = 1 << 30;
         for (const auto &c : base) pmin = std::min(pmin, c.elems_per_thread);
         for (const auto &c : base)
