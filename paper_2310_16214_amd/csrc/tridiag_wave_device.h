@@ -840,18 +840,22 @@ __device__ __forceinline__ void tridiag_wave_block(const T *A, const T *B, const
 // What bounds the longer systems is this chain of barriers, with one to a few
 // workgroups per CU to hide it, so it is kept short: the in-lane levels take
 // one exchange (cr_inlane_last; lanes within a wave by DPP, LDS only from a
-// wave's first lane to the previous wave's last), and PCR takes two steps per
-// exchange, each thread repeating its two neighbours' first step from the six
-// rows around it (four eliminations for two steps instead of two, on one
-// equation per lane against the 2 (P - 1) of the lane's own).  Barriers per
-// system: 2 + ceil(log2(n / P) / 2), against 1 + log2 P + log2(n / P) with an
-// exchange per level and step (7 against 15 for n = 16384, P = 16).  With the
-// staged stores, 2^23 float32 unknowns at n = 16384 take 39.2 us (49.2 before,
-// both at P = 16), 2^22 float64 unknowns at n = 8192 44.8 (51.9, P = 8), 777
+// wave's first lane to the previous wave's last), and from eight equations per
+// lane on PCR takes two steps per exchange, each thread repeating its two
+// neighbours' first step from the six rows around it (four eliminations for
+// two steps instead of two, on one equation per lane against the 2 (P - 1) of
+// the lane's own).  With two or four, PCR is most of the work, and the second
+// step's rows take a float64 workgroup of 1024 threads past the 64 registers
+// that let two share a CU: there it is one step per exchange (2^22 float64
+// unknowns of n = 4096, P = 4: 57.3 us in two steps per exchange, 37.5 in one;
+// float32, n = 512, P = 2 in 256 threads: 27.0 and 22.2).  Barriers per system from P = 8 on:
+// 2 + ceil(log2(n / P) / 2), against 1 + log2 P + log2(n / P) with an exchange
+// per level and step (7 against 15 for n = 16384, P = 16).  With the staged
+// stores, 2^23 float32 unknowns at n = 16384 take 39.2 us (49.2 before, both
+// at P = 16), 2^22 float64 unknowns at n = 8192 44.8 (51.9, P = 8), 777
 // float64 systems of 4096 27.0 (32.9); a copy of the same five arrays takes
-// 31 us for 160 MiB.  Every
-// thread of the workgroup reaches each of them (threads of absent systems
-// solve identity rows).  last: L values for the last exchange, outside both
+// 31 us for 160 MiB.  Every thread of the workgroup reaches each barrier
+// (threads of absent systems solve identity rows).  last: L values for the last exchange, outside both
 // sets where the caller goes on to use their space.
 template <typename T>
 struct TriRow {
@@ -861,6 +865,14 @@ template <typename T>
 __device__ __forceinline__ TriRow<T> row_eliminate(TriRow<T> r, const TriRow<T> &l, const TriRow<T> &u) {
     unit_eliminate(r.a, r.c, r.d, l.a, l.c, l.d, u.a, u.c, u.d);
     return r;
+}
+template <int P>
+constexpr bool tri_blk_two_steps() { return P >= 8; }
+// The exchanges before the last one.
+template <int P>
+__device__ __forceinline__ int tri_blk_exchanges(int lps) {
+    const int steps = __builtin_ctz(lps);
+    return 1 + (tri_blk_two_steps<P>() ? (steps + 1) / 2 : steps);
 }
 template <typename T, int P>
 __device__ __forceinline__ void block_cr_pcr(T (&a)[P], T (&c)[P], T (&d)[P], int t, int lps, int tx, int L,
@@ -928,20 +940,27 @@ __device__ __forceinline__ void block_cr_pcr(T (&a)[P], T (&c)[P], T (&d)[P], in
         __syncthreads();
         return w;
     };
-    int dl = 1;
-    if (__builtin_ctz(lps) & 1) {  // an odd number of steps: one by itself
-        const T *w = publish();
-        r = row_eliminate(r, row(w, -1), row(w, 1));
-        dl = 2;
-    }
-    for (; dl < lps; dl *= 4) {  // steps dl and 2 dl
-        const T *w = publish();
-        const TriRow<T> l1 = row(w, -dl), u1 = row(w, dl);
-        TriRow<T> l2 = row_eliminate(row(w, -2 * dl), row(w, -3 * dl), l1);
-        TriRow<T> u2 = row_eliminate(row(w, 2 * dl), u1, row(w, 3 * dl));
-        if (t < 2 * dl) l2 = {T(0), T(0), T(0)};
-        if (t + 2 * dl >= lps) u2 = {T(0), T(0), T(0)};
-        r = row_eliminate(row_eliminate(r, l1, u1), l2, u2);
+    if constexpr (tri_blk_two_steps<P>()) {
+        int dl = 1;
+        if (__builtin_ctz(lps) & 1) {  // an odd number of steps: one by itself
+            const T *w = publish();
+            r = row_eliminate(r, row(w, -1), row(w, 1));
+            dl = 2;
+        }
+        for (; dl < lps; dl *= 4) {  // steps dl and 2 dl
+            const T *w = publish();
+            const TriRow<T> l1 = row(w, -dl), u1 = row(w, dl);
+            TriRow<T> l2 = row_eliminate(row(w, -2 * dl), row(w, -3 * dl), l1);
+            TriRow<T> u2 = row_eliminate(row(w, 2 * dl), u1, row(w, 3 * dl));
+            if (t < 2 * dl) l2 = {T(0), T(0), T(0)};
+            if (t + 2 * dl >= lps) u2 = {T(0), T(0), T(0)};
+            r = row_eliminate(row_eliminate(r, l1, u1), l2, u2);
+        }
+    } else {
+        for (int dl = 1; dl < lps; dl *= 2) {
+            const T *w = publish();
+            r = row_eliminate(r, row(w, -dl), row(w, dl));
+        }
     }
     d[P - 1] = r.d;
     // ---- the previous lane's last unknown, then back substitution in the lane
@@ -1002,8 +1021,7 @@ __device__ __forceinline__ void tridiag_blk_block(const T *A, const T *B, const 
     } else {
         // the last exchange may take either set: the one of the exchange
         // before it is still being read
-        const int exchanges = 1 + (__builtin_ctz(lps) + 1) / 2;
-        block_cr_pcr<T, P>(a, c, d, t, lps, tx, L, xs, xs + (exchanges & 1) * 3 * L);
+        block_cr_pcr<T, P>(a, c, d, t, lps, tx, L, xs, xs + (tri_blk_exchanges<P>(lps) & 1) * 3 * L);
         if (active) wave_store<T, P>(X + base, d);
     }
 }

@@ -555,7 +555,7 @@ static int static_vgprs(int op, int dtype, int64_t n, int P, int algo) {
         return (algo & PPX_SCAN_KS_PIPE) ? pipe[f64][algo & PPX_SCAN_LF][lp] : plain[f64][lp];
     }
     if (tri_blk(algo, n, P)) {
-        static constexpr int blk[2][4] = {{31, 37, 50, 78}, {58, 70, 92, 151}};
+        static constexpr int blk[2][4] = {{19, 31, 50, 78}, {32, 56, 92, 151}};
         return blk[f64][std::min(lp, 3)];
     }
     if (tri_in_wave(algo)) {
