@@ -125,22 +125,32 @@ __device__ __forceinline__ void store_nt_any(V *p, const V &v) {
     }
 }
 
+// A vector offset as a value the compiler knows nothing of, so that constants
+// added to it stay at the access and fold into its immediate (up to 4095).  In
+// a loop the sums would otherwise be invariants, hoisted into a register each.
+__device__ __forceinline__ int local_voff(int voff) {
+    asm volatile("" : "+v"(voff));
+    return voff;
+}
+
 // K contiguous 4- or 8-byte values at byte offset voff (16-byte words where
-// the size allows).  The constant part of each offset is added to the vector
-// offset, where it folds into the instruction's immediate: a 16-byte store
-// must not take it from a scalar register.  With a scalar-register offset the
-// compiler lets the very next instruction overwrite the store's data
-// registers, and gfx950 then stored the overwritten value in lanes 12..15 of
-// each 16 (seen in the persistent scan of float64 rows: the first 8 bytes of
-// a word replaced by the v_mov that followed its store); with an immediate it
-// keeps them apart.
+// the size allows).  Loads take the constant part of each offset in the scalar
+// operand.  For stores it is added to the vector offset, where it folds into
+// the instruction's immediate: a 16-byte store must not take it from a scalar
+// register.  With a scalar-register offset the compiler lets the very next
+// instruction overwrite the store's data registers, and gfx950 then stored the
+// overwritten value in lanes 12..15 of each 16 (seen in the persistent scan of
+// float64 rows: the first 8 bytes of a word replaced by the v_mov that
+// followed its store); with an immediate it keeps them apart.  (Loads whose
+// offsets went the same way, hoisted, cost the persistent float64 solvers of
+// 16 equations per lane up to 19%: WM, 2^22 unknowns, 45.3 us against 38.3.)
 template <typename T, int K>
 __device__ __forceinline__ void buf_load(T (&v)[K], __amdgpu_buffer_rsrc_t r, int voff) {
     constexpr int B = K * (int)sizeof(T);
     if constexpr (B % 16 == 0) {
 #pragma unroll
         for (int w = 0; w < B / 16; ++w) {
-            const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(r, voff + 16 * w, 0, 0);
+            const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(r, voff, 16 * w, 0);
             __builtin_memcpy(&v[w * 16 / (int)sizeof(T)], &x, 16);
         }
     } else if constexpr (B == 8) {
@@ -157,6 +167,7 @@ template <typename T, int K, int POLICY = 0>
 __device__ __forceinline__ void buf_store(const T (&v)[K], __amdgpu_buffer_rsrc_t r, int voff) {
     constexpr int B = K * (int)sizeof(T);
     if constexpr (B % 16 == 0) {
+        voff = local_voff(voff);
 #pragma unroll
         for (int w = 0; w < B / 16; ++w) {
             u32x4 x;

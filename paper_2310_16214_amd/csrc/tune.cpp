@@ -562,12 +562,12 @@ static int static_vgprs(int op, int dtype, int64_t n, int P, int algo) {
         static constexpr int wave[2][2][6][4] = {
             {{{19, 35, 59, 93}, {22, 28, 46, 86}, {25, 43, 57, 81},
               {26, 48, 65, 90}, {17, 28, 39, 78}, {24, 30, 42, 73}},
-             {{24, 50, 115, 229}, {30, 45, 94, 184}, {24, 40, 75, 155},
-              {34, 62, 90, 148}, {26, 39, 73, 165}, {37, 51, 80, 138}}},
+             {{24, 50, 114, 226}, {30, 44, 93, 181}, {24, 40, 74, 152},
+              {34, 62, 90, 146}, {26, 39, 72, 162}, {37, 51, 79, 135}}},
             {{{34, 66, 100, 148}, {36, 48, 88, 140}, {44, 59, 102, 160},
               {46, 68, 104, 157}, {34, 46, 82, 152}, {48, 60, 84, 136}},
-             {{35, 123, 245, 364}, {52, 82, 152, 318}, {44, 75, 149, 296},
-              {62, 114, 220, 320}, {49, 77, 135, 263}, {69, 97, 157, 284}}}};
+             {{35, 122, 242, 356}, {52, 80, 149, 300}, {44, 74, 146, 290},
+              {62, 114, 218, 314}, {49, 76, 132, 260}, {69, 97, 153, 272}}}};
         return wave[f64][(algo & PPX_TRI_PIPE) != 0][tri_base(algo) - PPX_TRI_CR_PCR][std::min(lp, 3)];
     }
     return f64 ? (algo == PPX_TRI_PCR ? 34 : 33) : (algo == PPX_TRI_PCR ? 24 : 21);
