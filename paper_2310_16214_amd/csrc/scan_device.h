@@ -24,7 +24,10 @@
 //      slot and every wave adds the totals of the earlier waves of its problem
 //      (the paper's per-problem shared-memory slots, one per wave): the
 //      lanes of a 16-lane row read one slot each and sum them by rotations,
-//      four steps instead of up to 15 dependent reads;
+//      four steps instead of up to 15 dependent reads.  (Vectors of 8 bytes
+//      have them read in turn: with rotations their persistent kernels were up
+//      to 23% slower, 2^24 float32 of n = 256 in 1024 threads 30.5 us against
+//      24.9, and none of their shapes is the fastest of its size.)
 //   4. add the exclusive prefix to the values and store; a vector's prefix is
 //      the inclusive lane result of the lane before it plus the sums of
 //      earlier rows and waves, so every term of an output is a sum of
@@ -142,10 +145,14 @@ __device__ __forceinline__ void scan_values(U (&v)[P], int log2n, T *wave_tot, i
         if (lane == kWave - 1) wave_tot[w] = __builtin_bit_cast(T, carry);
         __syncthreads();
         const int w0 = w & ~((1 << (log2n - LW)) - 1);
-        const int u = lane & 15;  // at most 16 waves per workgroup
-        const bool earlier = u >= w0 && u < w;
-        const U slot = __builtin_bit_cast(U, wave_tot[earlier ? u : w]);
-        before = row16_sum(earlier ? slot : U(0));
+        if constexpr (V * sizeof(T) == 8) {
+            for (int u = w0; u < w; ++u) prefix[0] = prefix[0] + __builtin_bit_cast(U, wave_tot[u]);
+        } else {
+            const int u = lane & 15;  // at most 16 waves per workgroup
+            const bool earlier = u >= w0 && u < w;
+            const U slot = __builtin_bit_cast(U, wave_tot[earlier ? u : w]);
+            before = row16_sum(earlier ? slot : U(0));
+        }
     }
 
     // 4. add the prefix
@@ -211,8 +218,8 @@ __global__ __launch_bounds__(1024) void k_scan(const T *in, T *out, int log2n, l
 }
 
 // A thread's rows through a group's buffer descriptor (voff: the byte offset
-// of its first vector).  The rows' offsets go in the vector offset, where
-// they fold into the instructions' immediates.
+// of its first vector).  The rows' offsets go in the vector offset (a 16-byte
+// store must not take one from a scalar register, see buf_store).
 template <typename T, int P, typename U>
 __device__ __forceinline__ void scan_load_rows(U (&v)[P], __amdgpu_buffer_rsrc_t r, int voff) {
     constexpr int V = scan_vec<T, P>(), B = scan_row_elems<T, P>() * (int)sizeof(T);

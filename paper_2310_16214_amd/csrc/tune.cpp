@@ -549,8 +549,8 @@ static int static_vgprs(int op, int dtype, int64_t n, int P, int algo) {
     const bool f64 = dtype == PPX_F64;
     const int lp = std::max(0, ilog2(P) - 1);
     if (op == PPX_OP_SCAN) {
-        static constexpr int plain[2][5] = {{9, 11, 16, 30, 58}, {16, 20, 36, 68}};
-        static constexpr int pipe[2][2][5] = {{{16, 20, 34, 52, 91}, {22, 26, 38, 59, 103}},
+        static constexpr int plain[2][5] = {{8, 11, 16, 30, 58}, {16, 20, 36, 68}};
+        static constexpr int pipe[2][2][5] = {{{16, 20, 34, 52, 91}, {17, 26, 38, 59, 103}},
                                               {{20, 32, 60, 108}, {26, 36, 64, 112}}};
         return (algo & PPX_SCAN_KS_PIPE) ? pipe[f64][algo & PPX_SCAN_LF][lp] : plain[f64][lp];
     }
