@@ -103,9 +103,15 @@ int launch_scan(const void *in, void *out, int log2n, int64_t batch, int dtype, 
         const DeviceInfo *di = device_info();
         if (!di) return PPX_EDEVICE;
         const int64_t resident = (int64_t)scan_resident_per_cu(k, c.threads_per_block) * di->cus;
-        if (resident < grid) grid = resident;
-        // every workgroup has one group: nothing to prefetch (16 rows of 4096
-        // float32: 2.64 us persistent, 2.23 plain)
+        // Where every workgroup has one group there is nothing to prefetch (16
+        // rows of 4096 float32: 2.64 us persistent, 2.23 plain).  With one
+        // 16-byte vector per thread the walk over groups costs more than the
+        // prefetch gives on short walks too: float32 of n = 512, P = 4 in 1024
+        // threads, 2^22 elements (two groups a workgroup) 8.75 us persistent
+        // and 6.44 plain, 2^23 11.6 and 11.0, 2^24 (eight) 20.7 and 20.0; these
+        // walk eight groups at least.  Both kernels give the same bits.
+        const int64_t least = c.elems_per_thread * (dtype == PPX_F64 ? 8 : 4) == 16 ? 8 * resident : resident + 1;
+        if (grid >= least) grid = resident;
         else k = scan_kernel(dtype, c.elems_per_thread, c.algo & ~PPX_SCAN_KS_PIPE, exclusive);
     }
     const dim3 g((unsigned)grid), b(c.threads_per_block);

@@ -1,6 +1,6 @@
 """GPU parity of the persistent kernels on batches that make every resident
 workgroup loop: at least three groups each (from the kernel's own registers
-and LDS), with a ragged last group.  Smaller batches run the plain twin.
+and LDS; eight where the scan asks for that many), with a ragged last group.  Smaller batches run the plain twin.
 
 Scans and tridiagonal solves do the same arithmetic as the plain kernel and are
 compared with it bit for bit over the whole batch; FFTs within the FFT's bound
@@ -21,7 +21,9 @@ def looping_batch(op, dtype, n, cfg):
     r = ppx.kernel_resources(op, dtype, n, cfg)
     blocks, _ = ppx.occupancy(m, r)
     assert blocks >= 1
-    return 3 * blocks * m.num_cus * cfg.problems_per_block + 1
+    # a scan of one 16-byte vector per thread: from eight groups per workgroup on
+    groups = 8 if op == ppx.OP_SCAN and cfg.elems_per_thread * (8 if dtype == ppx.F64 else 4) == 16 else 3
+    return groups * blocks * m.num_cus * cfg.problems_per_block + 1
 
 
 def run_both(cuda, op, dtype, n, cfg, call, like):
@@ -41,7 +43,7 @@ def run_both(cuda, op, dtype, n, cfg, call, like):
 
 
 @pytest.mark.parametrize("dtype", [ppx.I32, ppx.F32, ppx.F64])
-@pytest.mark.parametrize("L,P,n", [(64, 4, 128), (256, 8, 512), (256, 16, 4096), (1024, 16, 2048), (1024, 32, 16384)])
+@pytest.mark.parametrize("L,P,n", [(64, 2, 64), (1024, 2, 512), (64, 4, 128), (512, 4, 1024), (256, 8, 512), (256, 16, 4096), (1024, 16, 2048), (1024, 32, 16384)])
 def test_scan(cuda, dtype, L, P, n):
     import torch
     if dtype == ppx.F64 and P > 16:
