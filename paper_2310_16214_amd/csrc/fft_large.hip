@@ -672,18 +672,27 @@ bool fft_null_plan(int64_t n, int64_t batch, ppx_fft_plan &p) {
 // A recorded (or the default) plan is for a full GPU: long columns in wide
 // tiles, each tile most of a CU's LDS.  Where one of its passes has fewer tiles
 // than CUs, the call is bound by the length of one tile's work, and takes short
-// columns instead (as even a split as
-// radix 8 allows: n2 = 512 up to n = 2^18, then n1 = 2^((log2 n - 1) / 2)), in
-// the widest tiles that still give every CU one, down to four columns and 256
-// threads.  One problem, recorded plan against this: 2^15 12.4 -> 10.0 us,
-// 2^16 17.1 -> 10.8, 2^17 20.4 -> 12.8, 2^18 20.9 -> 13.4, 2^20 27.1 -> 19.0,
-// 2^21 35.1 -> 28.7; at 2^22 elements per call (a tile for every CU in both
-// passes) the recorded plans win again or are even (2^20 x 4 41.8 against
-// 42.2, 2^21 x 2 43.0 both).
+// columns instead (as even a split as radix 8 allows: n2 = 512 up to n = 2^18,
+// then n1 = 2^((log2 n - 1) / 2)), in the widest tiles that still give every CU
+// one, down to four columns and 256 threads.  One problem, recorded plan
+// against this: 2^15 12.4 -> 10.0 us, 2^16 17.1 -> 10.8, 2^17 20.4 -> 12.8,
+// 2^18 20.9 -> 13.4, 2^20 27.1 -> 19.0, 2^21 35.1 -> 28.7; at 2^22 elements per
+// call (a tile for every CU in both passes) the recorded plans win again or are
+// even (2^20 x 4 41.8 against 42.2, 2^21 x 2 43.0 both).
+//
+// A plan with tiles of 64 columns (the recorded ones up to 2^17) has short
+// columns itself and wins from half the CUs on: 2^16 x 32 (half of them with a
+// tile) 27.4 against 26.0, x 40 27.8 against 33.1, x 56 31.5 against 34.8; 2^15
+// x 56 19.6 against 21.2; 2^17 x 16 29.1 against 24.4, x 20 32.2 against 33.2.
+// The others leave the field only with a tile for every CU, as the short
+// columns also have the smaller error (2^20: 2.0e-7 against 3.2e-7): gains of
+// 2-9% at 2^18 above half, losses of 4-9% at 2^19 x 5 to 7 and 27% at 2^20 x 3.
 void fft_fill_plan(int64_t n, int64_t batch, int cus, ppx_fft_plan &p) {
     const int64_t tiles_a = (int64_t(1) << p.log2_n1) / p.tile_a, tiles_b = (n >> p.log2_n1) / p.tile_b;
-    if (batch * std::min(tiles_a, tiles_b) >= cus) return;
-    const int ln = ilog2(n), l1 = ln <= 18 ? ln - 9 : (ln - 1) / 2, l2 = ln - l1;
+    const int64_t tiles = batch * std::min(tiles_a, tiles_b);
+    if (p.tile_a >= 64 ? 2 * tiles > cus : tiles >= cus) return;
+    const int ln = ilog2(n);
+    const int l1 = ln <= 18 ? ln - 9 : (ln - 1) / 2, l2 = ln - l1;
     ppx_fft_plan q{l1, l2 <= 9 ? 8 : 16, l1 <= 10 ? 8 : 16, 0, 0};
     const auto width = [&](int radix, int log2len, int log2cols, bool pass_a) {
         int width = 0;
