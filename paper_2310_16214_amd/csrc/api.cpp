@@ -44,6 +44,7 @@ float g_tw_hi_host[2 * (1024 + 8)];
 std::vector<DeviceInfo *> g_devices;  // indexed by device ordinal; never freed
 bool g_any_device = false;
 int64_t g_lds_limit = kStaticLdsPerBlock;
+int g_cus = kDefaultCus;
 }  // namespace
 
 int current_device_or_zero() {
@@ -53,6 +54,7 @@ int current_device_or_zero() {
 }
 
 int64_t lds_limit() { return g_lds_limit; }
+int cu_count() { return g_cus; }
 
 const DeviceInfo *device_info_if_ready() {
     if (!g_any_device) return nullptr;
@@ -112,6 +114,7 @@ const DeviceInfo *device_info() {
     g_devices[dev] = di;
     g_any_device = true;
     g_lds_limit = di->lds_per_block;
+    g_cus = di->cus;
     return di;
 }
 
@@ -146,10 +149,7 @@ static int resolve(int op, int dtype, int64_t n, int64_t batch, const ppx_config
     int64_t tuned_batch;
     if (cached_config(op, dtype, n, c, tuned_batch)) {
         as_is = batch >= tuned_batch;
-        if (!as_is) {
-            const DeviceInfo *di = device_info_if_ready();
-            fit_shape(op, dtype, n, batch, di ? di->cus : kDefaultCus, c);
-        }
+        if (!as_is) fit_shape(op, dtype, n, batch, cu_count(), c);
         return PPX_OK;
     }
     return analytical_config(op, dtype, n, batch, c);
