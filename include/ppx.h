@@ -344,11 +344,12 @@ typedef struct ppx_job {
  * records in the kernel arguments, one workgroup per tile, and consists of
  * kernel launches alone: one per family, or one for several families whose
  * tiles together are few (the float32 families of one workgroup size, or of
- * both sizes in the smallest launches).  A larger launch copies its tables to the device (one of 4 ring slots), expands the tile
- * lists and runs persistent kernels that claim tiles from per-family
- * counters.  Asynchronous and stream-ordered; allocates nothing after a
- * device's first mixed launch, which creates the ring slots.  At most 16384
- * jobs and 2^20 tiles per launch (PPX_EINVAL beyond).
+ * both sizes in the smallest launches).  A larger launch copies its tables to
+ * the device (one of 4 ring slots), expands the tile lists and runs one kernel
+ * per family, a workgroup per tile.  Asynchronous and stream-ordered;
+ * allocates nothing after a device's first mixed launch, which creates the
+ * ring slots.  At most 16384 jobs and 2^20 tiles per launch (PPX_EINVAL
+ * beyond).
  */
 int launch_mixed(const ppx_job *jobs, int njobs, void *stream);
 /* A job of at least this many elements (n * batch) whose configuration with
@@ -372,8 +373,8 @@ int launch_mixed(const ppx_job *jobs, int njobs, void *stream);
  * up (device state, occupancy queries, the array's address) without
  * allocating; later calls only plan on the host and enqueue, on `stream`,
  * what launch_mixed does: the argument kernels, of one family or of several,
- * for a launch with few jobs per family (the array unused), else a few table copy kernels, the
- * tile-list expansion and the persistent family kernels.
+ * for a launch with few jobs per family (the array unused), else a few table
+ * copy kernels, the tile-list expansion and the family kernels.
  * Every call on a device shares that device's array, so calls whose work
  * overlaps on one device (different streams, or host threads) race and must
  * be ordered by the caller.  Host-side planning touches no heap for shapes
@@ -391,8 +392,9 @@ int launch_mixed_noalloc(const ppx_job *jobs, int njobs, void *stream);
  * per tile (> 0) of the job in a launch of its own (the configuration's
  * problems per workgroup where its workgroup size is within the tile
  * kernel's limit; a launch runs each family at the largest workgroup size of
- * its jobs, so a job may get more problems per tile there, and a launch too
- * small to fill the GPU fewer) or a negative PPX_E* code, and writes to *cfg
+ * its jobs, or at that limit where it goes through the device tables, so a job
+ * may get more problems per tile there, and a launch too small to fill the GPU
+ * fewer) or a negative PPX_E* code, and writes to *cfg
  * (if not NULL) the single-call configuration whose arithmetic the tiles
  * follow:
  * the configuration of the job's call with cfg == NULL, with the persistent
@@ -411,8 +413,8 @@ int ppx_mixed_tile_config(const ppx_job *job, ppx_config *cfg);
 /*
  * ppx_mixed_argument_launch -- 1 if launch_mixed would pass these jobs'
  * records in the kernel arguments (no tiled job, or at most
- * PPX_MIXED_ARG_JOBS per family), 0 if it would use the device tables and
- * persistent kernels, or a negative PPX_E* code for jobs it would refuse.
+ * PPX_MIXED_ARG_JOBS per family), 0 if it would use the device tables, or a
+ * negative PPX_E* code for jobs it would refuse.
  * Planning only (needs no GPU where ppx_mixed_tile_config needs none).
  */
 int ppx_mixed_argument_launch(const ppx_job *jobs, int njobs);

@@ -3,7 +3,7 @@
  * operations of ppx.h.  Jobs (ppx_job: a whole batched FFT, scan or
  * tridiagonal call) arrive one by one; the server admits them in arrival
  * order while their memory fits an HBM budget, packs every job admitted
- * since its last launch into ONE mixed persistent launch (launch_mixed),
+ * since its last launch into ONE mixed launch (launch_mixed),
  * keeps up to `max_inflight` launches running on separate streams so that new
  * work overlaps work already on the device, retires jobs when their launch's
  * completion event fires, and returns their memory to the budget when the

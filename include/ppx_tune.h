@@ -102,7 +102,7 @@ int ppx_analytical_select(int op, int dtype, int64_t n, int64_t batch, const ppx
 
 /*
  * Consistency check of the mixed launch (launch_mixed): PPX_OK if every
- * family of tile shapes has its persistent kernel in the library, else
+ * family of tile shapes has its kernels in the library, else
  * PPX_EINVAL naming the first family without one.  Needs no GPU.
  */
 int ppx_mixed_families_complete(void);

@@ -7,10 +7,8 @@
 // family, or per class of families that share one (mixed_class.hip), a
 // workgroup per tile, nothing else.  Any other launch copies one
 // table (header and job records) from pinned memory to the device and
-// enqueues [expand the tile lists] -> [family kernel] -> ..., each family
-// kernel persistent (at most as many workgroups as are resident, and no more
-// than its tiles), draining its family's tiles, so every workgroup exits
-// once they are done.  Either way the families go in ascending order of
+// enqueues [expand the tile lists] -> [family kernel] -> ..., a workgroup per
+// tile of the family.  Either way the families go in ascending order of
 // their jobs' elements, and the jobs that run as their own calls last.
 #include <hip/hip_runtime.h>
 
@@ -46,7 +44,7 @@ int64_t mix_lds_bytes(int fam) {
     }
 }
 
-// The family's kernel (persistent, or taking its records in the arguments),
+// The family's kernel (reading the tables, or taking its records in the arguments),
 // from whichever translation unit instantiates it.
 static const void *mix_kernel(int fam, bool args) {
     if (const void *k = mix_fft_kernel(fam, args)) return k;
@@ -106,7 +104,7 @@ int mix_plan(const ppx_job &j, MixPlan &m) {
     }
     m.direct = false;
     if (j.op == PPX_OP_FFT) {
-        c.algo &= ~PPX_FFT_LDS_PIPE;  // the launch is persistent itself
+        c.algo &= ~PPX_FFT_LDS_PIPE;  // a workgroup runs one tile
         if (!fft_mix_shape(c.radix, c.elems_per_thread, j.n)) {
             // a shape the families do not hold: the nearest radix = P one, at
             // one problem per 64-thread group at least
@@ -255,6 +253,14 @@ int mix_build_tables(const ppx_job *jobs, int njobs, char *buf, int64_t *ntiles_
         if (rec_job) rec_job[nrec] = i;
         ++nrec;
     }
+    // A launch through the device tables, with its many jobs, is cut into as few
+    // tiles as its families' kernels allow (33 FFTs of n = 256 tuned to 128
+    // threads: 118 us in tiles of 128, 62 in 256).
+    int jobs_of[kMixFamilies] = {};
+    bool tables = false;
+    for (int k = 0; k < nrec; ++k) tables = ++jobs_of[rec[k].family] > kMixArgJobs || tables;
+    for (int f = 0; tables && f < kMixFamilies; ++f)
+        if (jobs_of[f]) h->block[f] = (unsigned)mix_block(f);
     // pass 2: problems per tile at the family's workgroup size, tile ranges
     int64_t fam_tiles[kMixFamilies] = {};
     for (int k = 0; k < nrec; ++k) {
@@ -325,12 +331,6 @@ MixedCtx *mixed_ctx() {
 }
 }  // namespace
 
-// Resident workgroups of each family's persistent kernel on the current
-// device at each workgroup size 64 << k up to the family's (from the
-// occupancy query at that size and its LDS), set up once per process.
-constexpr int kMixBlockSizes = 5;  // 64 .. 1024
-static int g_resident[kMixFamilies][kMixBlockSizes];
-
 // LDS bytes of family fam's kernel at workgroup size block: the tiles'
 // buffers scale with it, except the LDS-exchange tridiagonal family's.
 static size_t mix_lds_at(int fam, int block) {
@@ -342,22 +342,19 @@ static std::mutex g_prep_mu;
 int mix_prepare_kernels() {
     std::lock_guard<std::mutex> lk(g_prep_mu);
     if (g_prepared) return PPX_OK;
-    const DeviceInfo *di = device_info();
-    if (!di) return PPX_EDEVICE;
+    if (!device_info()) return PPX_EDEVICE;
     for (int f = 0; f < kMixFamilies; ++f) {
         for (int args = 0; args < 2; ++args) {
             const void *k = mix_kernel(f, args != 0);
             if (!k) return fail(PPX_EHIP, "mixed launch: no kernel for family " + std::to_string(f));
             (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)mix_lds_bytes(f));
-            for (int b = 0; b < kMixBlockSizes && (kWave << b) <= mix_block(f); ++b) {
-                const int block = kWave << b;
+            for (int block = kWave; block <= mix_block(f); block *= 2) {
                 int per_cu = 0;
                 if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, block, mix_lds_at(f, block)) !=
                         hipSuccess ||
                     per_cu < 1)
                     return fail(PPX_EHIP,
                                 "mixed launch: the kernel of family " + std::to_string(f) + " cannot be resident");
-                if (!args) g_resident[f][b] = per_cu * di->cus;
             }
         }
     }
@@ -372,8 +369,8 @@ int mix_prepare_kernels() {
 }
 
 // Enqueues the expansion and the kernels of the families in `mask` on
-// stream s, reading the tables at d_tables; each family's grid is its
-// resident count capped at its tile count ntiles[f].
+// stream s, reading the tables at d_tables; each family's grid is its tile
+// count ntiles[f].
 int mix_enqueue(char *d_tables, int mask, const int64_t *ntiles, const unsigned *blocks, const int *order, int norder,
                 const float2 *tw, hipStream_t s, mix_after_family_t after, void *arg) {
     hipLaunchKernelGGL(k_mix_expand, dim3(kMixExpandBlocks), dim3(kMixExpandThreads), 0, s, d_tables);
@@ -385,9 +382,8 @@ int mix_enqueue(char *d_tables, int mask, const int64_t *ntiles, const unsigned 
         const int f = order[k];
         if (!(mask & (1 << f))) continue;
         const int block = (int)blocks[f];
-        const int64_t grid = std::min<int64_t>(g_resident[f][ilog2(block / kWave)], std::max<int64_t>(1, ntiles[f]));
-        hipLaunchKernelGGL(reinterpret_cast<mix_kernel_t>(const_cast<void *>(mix_kernel(f, false))), dim3((unsigned)grid),
-                           dim3(block), mix_lds_at(f, block), s, a, tw);
+        hipLaunchKernelGGL(reinterpret_cast<mix_kernel_t>(const_cast<void *>(mix_kernel(f, false))),
+                           dim3((unsigned)ntiles[f]), dim3(block), mix_lds_at(f, block), s, a, tw);
         e = hipGetLastError();
         if (e == hipSuccess && after)
             if (int rc = after(arg, 1 << f, s)) return rc;
@@ -682,8 +678,7 @@ int mix_launch_direct(const ppx_job &j, const ppx_config &c, hipStream_t s) {
 // host code the array's name is not a device address).  The table reaches the
 // device through the kernel arguments of a few copy launches (the runtime
 // copies kernel arguments when a launch is enqueued), so no host buffer
-// outlives the call and no copy is issued from host memory; the tile
-// counters are part of that table and start at zero with it.  Every call on
+// outlives the call and no copy is issued from host memory.  Every call on
 // a device shares its array: calls that overlap on one device race.
 constexpr int kNoAllocJobs = PPX_NOALLOC_MAX_JOBS;
 constexpr int kNoAllocTiles = PPX_NOALLOC_MAX_TILES;

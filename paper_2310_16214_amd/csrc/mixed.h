@@ -20,11 +20,10 @@
 //   light and a heavy register tier (mix_triw_family);
 //   tridiagonal through LDS (CR and PCR of larger systems);
 //   the CR -> PCR hybrid of systems spanning several waves.
-// Each family has two kernels running its tiles: one whose jobs come in the
-// kernel arguments, a workgroup per tile, for launches with few jobs per
-// family; and a persistent one pulling tile indices from the family's
-// counter until its tiles are drained, after a table expansion on the same
-// stream.
+// Each family has two kernels running its tiles, a workgroup per tile: one
+// whose jobs come in the kernel arguments, for launches with few jobs per
+// family; and one that finds its tile's job in the device tables, after a
+// table expansion on the same stream.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -72,7 +71,6 @@ static_assert(sizeof(MixJob) == 72, "job record layout");
 // tile lists (one 32-bit job index per tile, family after family) at
 // tiles_off.
 struct MixHeader {
-    unsigned next[kMixFamilies];      // tile counters (0 at launch)
     unsigned ntiles[kMixFamilies];    // tiles per family
     unsigned tile_base[kMixFamilies]; // first entry of each family's list
     unsigned block[kMixFamilies];     // workgroup size of each family's tiles (host use)
@@ -126,11 +124,11 @@ int64_t mix_lds_bytes(int fam);
 // has at most kMixArgJobs jobs passes each family's job records here
 // (first_tile counted within the family) to the family's argument kernel,
 // whose workgroup b runs tile b: no table in device memory, no expansion, no
-// counter, one launch per family or per class of families (below).  Any other launch passes the device tables
-// (tables) to the persistent kernels, which claim tiles from the counters.
+// counter, one launch per family or per class of families (below).  Any other
+// launch passes the device tables (tables).
 constexpr int kMixArgJobs = PPX_MIXED_ARG_JOBS;
 struct MixArgs {
-    const char *tables;  // persistent kernels: the device tables
+    const char *tables;  // table kernels: the device tables
     unsigned ntiles;     // argument kernels: the family's tiles
     unsigned njobs;      // argument kernels: records in jobs[]
     MixJob jobs[kMixArgJobs];
@@ -157,8 +155,8 @@ static_assert(sizeof(MixClassArgs) <= 4096 - 64, "kernel arguments are limited t
 typedef void (*mix_class_kernel_t)(MixClassArgs a);
 const void *mix_class_kernel(int cls);
 
-// Kernel of a family (signature mix_kernel_t), persistent or taking its
-// records in the arguments, from the translation unit that instantiates it.
+// Kernel of a family (signature mix_kernel_t), taking its records from the
+// tables or in the arguments, from the translation unit that instantiates it.
 typedef void (*mix_kernel_t)(MixArgs a, const float2 *tw);
 const void *mix_fft_kernel(int fam, bool args);
 const void *mix_scan_kernel(int fam, bool args);
@@ -183,7 +181,8 @@ constexpr int kMixExpandThreads = 256;
 // a problem's threads (tpp); the problems per tile are block / tpp, so a job
 // alone runs tiles of exactly its tuned shape (G_b problems of P values per
 // thread in L threads).  A launch runs each family at the largest block of
-// its jobs.  LDS-exchange tridiagonal tiles (tpp = 0) are sized by LDS.
+// its jobs, and at the family's own (mix_block) where it goes through the
+// device tables.  LDS-exchange tridiagonal tiles (tpp = 0) are sized by LDS.
 struct MixPlan {
     int family, shape, per_tile, flags;
     int tpp, block;
@@ -214,8 +213,8 @@ int mix_launch_direct(const ppx_job &j, const ppx_config &c, hipStream_t s);
 // Occupancy of every family kernel on the current device (once).
 int mix_prepare_kernels();
 // Expansion plus the family kernels of `mask` in the given order, on stream
-// s, in workgroups of blocks[f] threads, each grid capped at the family's
-// tile count ntiles[f].
+// s, in workgroups of blocks[f] threads, one for each of the family's ntiles[f]
+// tiles.
 int mix_enqueue(char *d_tables, int mask, const int64_t *ntiles, const unsigned *blocks, const int *order, int norder,
                 const float2 *tw, hipStream_t s, mix_after_family_t after = nullptr, void *arg = nullptr);
 // Whether the launch planned in `table` (header and records) can pass its
@@ -233,18 +232,19 @@ int mix_enqueue_args(const char *table, int mask, const int *order, int norder, 
 // (the grid is the family's tile count), its job found by a scan of the
 // family's few records, read through the constant address space (the
 // launch's explicit arguments start the kernarg segment, MixArgs first).
-// Otherwise the kernel is persistent: it claims tile indices of family FAM
-// from its counter in the device tables until they run out, the next index
-// being claimed while the current tile is processed, and looks the job up
-// in the family's tile list.
-// Either way body(job, first problem, problem count, tx, nt) runs each tile,
-// nt being the workgroup's size (the tuned one, at most mix_block(FAM); see
-// MixPlan) and tx the thread's
-// index in the workgroup passed through an empty asm that
-// claims to change it: without it the compiler hoists every address derived
-// from the thread index out of the loop, for every shape a family holds, and
-// keeps them all live (the FFT families then spilled).  Every thread of the
-// workgroup runs the same iterations, so all reach every barrier.
+// Otherwise workgroup b runs tile b of family FAM in the device tables, its job
+// looked up in the family's tile list.  (As many workgroups as are resident,
+// claiming tiles from a counter, are the slower form: where few of them fit a
+// CU, the claims and their barriers overlap with nothing.  Over 273 launches of
+// 35 to 500 jobs this and tiles of the family's full size (mix_build_tables)
+// take 0.54 of the former time for FFTs alone, 0.81 for tridiagonal jobs, 0.52
+// for scans, 0.58 for all three; none takes longer but one, 6%.)
+// Either way body(job, first problem, problem count, tx, nt) runs the tile,
+// nt being the workgroup's size (at most mix_block(FAM); see MixPlan) and tx
+// the thread's index in the workgroup passed through an empty asm that claims
+// to change it: without it the compiler computes every address derived from
+// the thread index ahead of the dispatch, for every shape a family holds, and
+// keeps them all live (the FFT families then spilled).
 typedef const __attribute__((address_space(4))) MixJob *mix_arg_job_ptr;
 
 __device__ __forceinline__ MixJob mix_load_job(mix_arg_job_ptr r) {
@@ -281,24 +281,12 @@ __device__ __forceinline__ void mix_tile_loop(const MixArgs &a, Body &&body) {
         while (k + 1 < a.njobs && recs[k + 1].first_tile <= t) ++k;
         mix_run_tile(mix_load_job(recs + k), t, (int)blockDim.x, body);
     } else {
-        __shared__ unsigned s_tile;
         const MixHeader *h = reinterpret_cast<const MixHeader *>(a.tables);
         const MixJob *jobs = reinterpret_cast<const MixJob *>(a.tables + kMixHeaderBytes);
         const unsigned *tiles = reinterpret_cast<const unsigned *>(a.tables + h->tiles_off) + h->tile_base[FAM];
-        unsigned *ctr = const_cast<unsigned *>(&h->next[FAM]);
-        const unsigned ntiles = h->ntiles[FAM];
-        if (threadIdx.x == 0) s_tile = atomicAdd(ctr, 1u);
-        __syncthreads();
-        unsigned t = __builtin_amdgcn_readfirstlane(s_tile);
-        while (t < ntiles) {
-            unsigned next = 0;
-            if (threadIdx.x == 0) next = atomicAdd(ctr, 1u);
+        const unsigned t = blockIdx.x;
+        if (t < h->ntiles[FAM])
             mix_run_tile(jobs[__builtin_amdgcn_readfirstlane(tiles[t])], t, (int)blockDim.x, body);
-            __syncthreads();  // every thread is done with s_tile and the tile's LDS
-            if (threadIdx.x == 0) s_tile = next;
-            __syncthreads();
-            t = __builtin_amdgcn_readfirstlane(s_tile);
-        }
     }
 }
 

@@ -1,4 +1,4 @@
-// FFT families of the mixed launch: persistent kernels whose tiles run the
+// FFT families of the mixed launch: kernels whose tiles run the
 // log2 n-specialised stage sequence of the job's tuned (radix = P) shape,
 // with its exchange (complex values, or real and imaginary parts in turn).
 // 256-thread workgroups take the shapes with at most 256 threads per problem

@@ -1,4 +1,4 @@
-// Scan families of the mixed launch: persistent kernels whose tiles run the
+// Scan families of the mixed launch: kernels whose tiles run the
 // job's tuned scan shape (values per thread, lane network, inclusive or
 // exclusive) on whole problems of T = n/P threads: 256-thread workgroups for
 // T <= 256, 1024-thread ones above.

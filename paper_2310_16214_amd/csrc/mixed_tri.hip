@@ -1,4 +1,4 @@
-// Tridiagonal families of the mixed launch: persistent kernels whose tiles
+// Tridiagonal families of the mixed launch: kernels whose tiles
 // run the job's tuned solver.  Systems that fit a wave (n / P <= 64) run the
 // in-wave variants (the CR -> PCR hybrid, CR, PCR with shuffles or with the
 // LDS exchange, Wang & Mou, Ladner-Fischer) in 256-thread workgroups, one

@@ -1,5 +1,5 @@
 // Continuous-batching request loop (include/ppx_serve.h): FIFO admission by
-// HBM budget, one mixed persistent launch per progress step over everything
+// HBM budget, one mixed launch per progress step over everything
 // admitted since the last launch, several launches in flight on separate
 // streams, completion by events.  The per-request mode is the baseline.
 #include <hip/hip_runtime.h>
