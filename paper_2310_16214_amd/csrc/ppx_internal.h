@@ -117,7 +117,7 @@ constexpr bool tri_blk(int algo, int64_t n, int64_t P) {
 }
 // Largest P * sizeof(element) of the persistent in-wave variants (the second
 // register set): every in-wave P.  With 16 values per lane and array the two
-// register sets need 135-218 VGPRs in float32 (two or three waves per SIMD)
+// register sets need 135-226 VGPRs in float32 (two or three waves per SIMD)
 // and, in float64, AGPRs as well (one wave per SIMD); a persistent grid needs
 // no more waves than that, and the tuners weigh the prefetch against the
 // lower occupancy.
